@@ -191,7 +191,7 @@ def layer_kernel(wl, direction):
     tables, page = (wl.block_tables, wl.page_size) if direction == "pack" else (wl.dst_block_tables, wl.dst_page_size)
     full_bound = wl.num_reqs == 1 and tables.shape[1] * page <= int(wl.seq_lens[0])   # packed slice = the lengths
     if full_bound and not any(wl.window(l) for l in range(wl.num_layers)) and row % (64 * 16) == 0:
-        return "kv_reshard_single_kernel"
+        return "kv_reshard_direct_kernel"
     return f"kv_{direction}_kernel"
 
 

@@ -25,9 +25,11 @@
 // Granules are at least one head's values (256 bytes for head_dim 128 in
 // bf16), so both sides touch whole cache lines: no LDS staging of the data is
 // needed even where the layout transposes (slot-major <-> head-major).
-// Each lane issues all of its loads before its stores; workgroups stride over
-// tiles on a grid capped at a few workgroups per CU.  Table entries and
-// lengths are bounds-checked on the device before any access.
+// Each lane issues all of its loads before its stores.  Moves of up to 1024
+// requests run a direct grid (kv_reshard_direct_kernel: one workgroup per
+// tile, no prefix scan, any row size); larger batches, and runs of fewer than
+// 16 bytes, a persistent one whose workgroups stride over tiles.  Table
+// entries and lengths are bounds-checked on the device before any access.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
@@ -42,17 +44,8 @@ namespace topkv_reshard {
 #ifndef TOPKV_RS_VPT
 #define TOPKV_RS_VPT 8            // pieces per lane per tile
 #endif
-#ifndef TOPKV_RS_SINGLE
-#define TOPKV_RS_SINGLE 1         // direct grid for one request without a window
-#endif
-#ifndef TOPKV_RS_DIRECT
-#define TOPKV_RS_DIRECT 1          // batches without a window take the direct grid when it fits
-#endif
-#ifndef TOPKV_XCD_REMAP
-#define TOPKV_XCD_REMAP 0         // 1: each XCD takes a contiguous eighth of a direct grid (measured slower)
-#endif
-#ifndef TOPKV_EARLY_LENS
-#define TOPKV_EARLY_LENS 1        // direct batches: earlier requests' lengths load with the request's own
+#ifndef TOPKV_RS_FILL
+#define TOPKV_RS_FILL 512         // direct grids: smaller tiles until there are this many workgroups
 #endif
 #ifndef TOPKV_RS_WG_PER_CU
 #define TOPKV_RS_WG_PER_CU 16     // grid cap = CUs * this
@@ -102,6 +95,7 @@ struct Side {
   int32_t bt_stride;
   int32_t packed;           // 1: packed buffer (shard regions of Params::packed_cap bytes)
   FastDiv page;             // tokens per page
+  FastDiv upp;              // direct grids: units per page
 };
 
 struct Params {
@@ -117,6 +111,17 @@ struct Params {
   int32_t max_tok;          // lengths are clamped to [0, max_tok]
   int32_t n_host;           // one request with a host-side length: its tokens (else unused)
   int32_t layers;           // direct grids: layers on grid z (1: one layer)
+  // direct grids (direct_move):
+  FastDiv unit;             // tokens per unit
+  FastDiv cpu;              // 16-byte chunks per unit of one plane
+  FastDiv cpg;              // 16-byte chunks per granule (kHeads)
+  FastDiv reqs;             // requests (grid z is layer * requests + request)
+  int64_t total_cap;        // packed bytes from the first layer's region to the end of the last one's
+  int32_t max_units;        // units of a request of max_tok tokens
+  int32_t gran;             // bytes of one granule of one token
+  int32_t region_gran;      // bytes of one token in a packed region (all its granules)
+  int32_t grain;            // a run cut short by the packed capacity is a multiple of this (a power of two)
+  int32_t strict;           // 1: a request whose packed block would end past the capacity is not moved at all
 };
 
 // Per-request kept-token counts and first kept tokens, and the exclusive
@@ -214,7 +219,7 @@ __device__ __forceinline__ Loc locate(uint32_t q2, const int32_t* tp, const int3
 // usually sit on the same page, so the last entry is kept.
 struct PageCache {
   int32_t r = -1;
-  uint32_t i = 0;
+  uint32_t i = ~0u;
   int32_t page = -1;
 };
 
@@ -324,144 +329,272 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_kernel(Params p, const in
   }
 }
 
-// Kept tokens (window 0) of requests [0, r): the (plane, token) offset of
-// request r in the packed order is planes times this.  Each wave sums the
+// Kept tokens of requests [0, r): the (plane, token) offset of request r in the packed order is planes times this.  Each wave sums the
 // lengths on its own (lanes stride over them, then a butterfly), so no LDS and
 // no barrier are involved.
 // `mine` is seq_lens[lane] for lanes below r, already loaded by the caller.
 __device__ __forceinline__ int32_t kept_before(const int32_t* __restrict__ seq_lens, int32_t r, int32_t max_tok,
-                                               int32_t mine) {
+                                               int32_t window, int32_t mine) {
   const int lane = threadIdx.x & 63;
   int32_t s = 0;
   for (int j = lane; j < r; j += 64) {
     int32_t n = j == lane ? mine : seq_lens[j];
-    s += n < 0 ? 0 : (n > max_tok ? max_tok : n);
+    n = n < 0 ? 0 : (n > max_tok ? max_tok : n);
+    s += (window > 0 && n > window) ? window : n;
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
   return __builtin_amdgcn_readfirstlane(s);
 }
 
-// Direct grid without a window, wave-uniform tokens (every 70B-class shape):
-// workgroup (x, y[, z]) copies tile x of plane y [of request z], in packed
-// order.  A token's page depends only on the token, not on the request's
-// length, so each wave's first page lookups go out together with the length
-// load; there is no prefix scan.  Pieces of tokens at or past the (clamped)
-// length are skipped.  kBatch: requests on grid z, each at the (plane, token)
-// offset of the lengths before it, and tiles past a request's length exit at
-// once; otherwise one request.  kHostLen: the one request's length is the
-// launch constant n_host instead of a device value.
-// Workgroup coordinates of a direct grid.  The dispatcher hands linear
-// workgroup ids to the 8 XCDs round-robin; with TOPKV_XCD_REMAP the ids are
-// permuted so XCD k runs the k-th contiguous eighth of the grid (a bijection
-// when the workgroup count is a multiple of 8, else the identity).
-__device__ __forceinline__ uint3 grid_block() {
-#if TOPKV_XCD_REMAP
-  const uint32_t gx = gridDim.x, gy = gridDim.y;
-  const uint32_t g = gx * gy * gridDim.z;
-  uint32_t l = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-  if ((g & 7u) == 0) l = (l & 7u) * (g >> 3) + (l >> 3);
-  const uint32_t xy = l % (gx * gy);
-  return make_uint3(xy % gx, xy / gx, l / (gx * gy));
-#else
-  return make_uint3(blockIdx.x, blockIdx.y, blockIdx.z);
-#endif
+// A 16-byte vector at any byte address: gfx950's vector memory instructions
+// take unaligned addresses, so a chunk needs no alignment of its run.
+typedef unsigned int Chunk16 __attribute__((ext_vector_type(4), aligned(1)));
+
+// Page index i of a wave-uniform unit through the scalar cache, the last entry kept.
+__device__ __forceinline__ int32_t page_of_wave(const Side& s, int32_t r, uint32_t i, PageCache& pc) {
+  if (i != pc.i) {
+    const ConstInt* tab = (const ConstInt*)s.tables;
+    pc.page = __builtin_amdgcn_readfirstlane(tab[(int64_t)r * s.bt_stride + i]);
+    pc.i = i;
+  }
+  return pc.page;
 }
 
-template <int VB, bool kBatch, bool kHostLen = false>
-__device__ __forceinline__ void direct_move(const Params& p, const int32_t* __restrict__ seq_lens) {
-  typedef typename Vec<VB>::type V;
-  constexpr uint32_t kTile = (uint32_t)kThreads * kVpt;
-  const uint32_t per_tp = p.ktp.d;
+__device__ __forceinline__ bool page_ok(const Side& s, int32_t page) {
+  return page >= 0 && (int64_t)page < s.num_pages;
+}
+
+// Byte of token t (in table entry i of a unit) of plane c, granule k, on a pool side.
+__device__ __forceinline__ int64_t pool_byte(const Side& s, uint32_t c, uint32_t t, uint32_t k, uint32_t i,
+                                             int32_t page) {
+  return (int64_t)page * s.page_bytes + (int64_t)c * s.plane_bytes + (int64_t)(t - i * s.page.d) * s.slot_bytes +
+         s.head0_bytes + (int64_t)k * s.gran_stride;
+}
+
+// The same with the page looked up, for the byte-by-byte chunks; false for a
+// page outside the pool.
+template <bool kPool>
+__device__ __forceinline__ bool slow_page(const Side& s, int32_t r, uint32_t c, uint32_t unit, uint32_t t, uint32_t k,
+                                          int64_t* off) {
+  *off = 0;
+  if (!kPool) return true;
+  const uint32_t i = fdiv(unit, s.upp);
+  const int32_t page = s.tables[(int64_t)r * s.bt_stride + i];
+  *off = pool_byte(s, c, t, k, i, page);
+  return page_ok(s, page);
+}
+
+__device__ __forceinline__ void copy_bytes(char* dst, const char* src, int32_t n) {
+  for (int32_t x = 0; x < n; ++x) dst[x] = src[x];
+}
+
+// Direct grid: workgroup (x, y, z) copies tile x of plane y of request z (of
+// layer z / num_reqs when several layers go out in one grid), in packed order.
+// A request's plane is cut into units: the most tokens that are one
+// contiguous run on both sides (the smaller side's page, or what divides both
+// page sizes, when whole rows move; one token when heads are sliced or laid
+// out head-major), and a unit into 16-byte chunks (of its granules when it
+// has several).  So a tile is full whatever the page size; the last unit or a
+// window's first one is simply shorter.  A run's last chunk is moved back to
+// end with the run: it repeats bytes of the chunk before it, with the same
+// values, and no chunk needs any alignment.
+//   kDir: pool -> packed, packed -> pool, or pool -> pool.
+//   kWave: a unit's chunks fill whole 64-chunk wave spans, so every wave
+//     instruction has one unit and page per side: scalar arithmetic and loads.
+//     Otherwise every lane finds its own unit, and the lanes' table entries
+//     are gathered (they share cache lines) before the data.
+//   kHeads: several granules per unit (head-major sides, shard regions).
+//   kHostLen: one request with the launch constant n_host; otherwise device
+//     lengths, requests on grid z, each at the offset of the lengths before it.
+// A unit's page depends on the length only through a window's start, so
+// without a window the first lookups go out together with the length load.
+// Tiles past a request's tokens exit at once.  Runs of fewer than 16 bytes
+// (the last token or two of narrow rows) and runs that the packed capacity
+// cuts short go byte by byte after the rest.
+// Bound: HBM, below about 30 MB a launch the launch and one chain of table
+// entry, data, store.  Measured against the persistent grid (its length scan,
+// a request search and two dependent divisions per piece) on launches that
+// only it took: 8 requests of 1-8k tokens in slices of two of eight 256-byte
+// heads (68 MB read and written) 20.7 -> 16.7 us a launch, 16 MLA requests
+// re-blocked 64 -> 16 (184 MB) 46.3 -> 36.5 us; and, with sides and lengths
+// as template parameters and the store addresses kept out of the load phase,
+// against the one-request grid before it, one 70B request's layer (33.5 MB)
+// 7.8 -> 7.5 us.
+enum { kPack = 0, kUnpack = 1, kPools = 2 };
+
+template <int kDir, bool kWave, bool kHeads, bool kHostLen, int VPT>
+__global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(Params p, const int32_t* __restrict__ seq_lens) {
+  constexpr uint32_t kTile = (uint32_t)kThreads * VPT;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wave_first = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
-  const uint3 b = grid_block();
-  const uint32_t c = b.y;
-  // grid z: the layer (one request), or layer * num_reqs + request (a batch over several layers)
+  const uint32_t c = blockIdx.y;
   uint32_t lz = 0;
   int32_t r = 0;
-  if (!kBatch) {
-    lz = b.z;
+  if (kHostLen || p.num_reqs == 1) {
+    lz = blockIdx.z;
   } else if (p.layers > 1) {
-    lz = b.z / (uint32_t)p.num_reqs;
-    r = (int32_t)(b.z - lz * (uint32_t)p.num_reqs);
+    lz = fdiv(blockIdx.z, p.reqs);
+    r = (int32_t)(blockIdx.z - lz * (uint32_t)p.num_reqs);
   } else {
-    r = (int32_t)b.z;
+    r = (int32_t)blockIdx.z;
   }
-  const char* const src_base = p.src.base + (int64_t)lz * p.src.layer_stride;
-  char* const dst_base = p.dst.base + (int64_t)lz * p.dst.layer_stride;
-  const uint32_t base = b.x * kTile;
+  const uint32_t base = blockIdx.x * kTile;
   PageCache src_pc, dst_pc;
-  {
-    // the first span's token is known before the length: prime the page caches
-    const uint32_t t0 = fdiv(base + wave_first, p.ktp);
-    if (t0 < (uint32_t)p.max_tok) {
-      const Loc at0{r, c, t0};
-      int64_t unused;
-      if (!p.src.packed) pool_offset_wave(p.src, at0, 0, 0, src_pc, &unused);
-      if (!p.dst.packed) pool_offset_wave(p.dst, at0, 0, 0, dst_pc, &unused);
+  if (kWave && p.window == 0) {
+    // the first span's unit is known before the length: prime the page caches
+    const uint32_t u = fdiv(base + wave_first, p.cpu);
+    if (u < (uint32_t)p.max_units) {
+      if (kDir != kUnpack) page_of_wave(p.src, r, fdiv(u, p.src.upp), src_pc);
+      if (kDir != kPack) page_of_wave(p.dst, r, fdiv(u, p.dst.upp), dst_pc);
     }
   }
   // with a batch, each lane below r also loads one earlier request's length
-  // (for the request's packed offset) next to this request's own
+  // (for the request's packed offset) next to this request's own, so the
+  // offset costs no memory latency of its own
   int32_t mine = 0;
-#if TOPKV_EARLY_LENS
-  if (kBatch && (int32_t)lane < r) mine = __builtin_nontemporal_load(seq_lens + lane);
-#endif
-  int32_t n = kHostLen ? p.n_host : __builtin_amdgcn_readfirstlane(seq_lens[r]);
-#if TOPKV_EARLY_LENS
-  if (kBatch) asm volatile("" ::"v"(mine));   // keep the load here: not sunk past the exit test below
-#else
-  if (kBatch && (int32_t)lane < r) mine = seq_lens[lane];
-#endif
-  n = n < 0 ? 0 : (n > p.max_tok ? p.max_tok : n);
-  const uint32_t end = (uint32_t)n * per_tp;                  // pieces of this plane
-  if (kBatch && base >= end) return;                          // past this request's tokens
-  const uint32_t q0 = (kBatch && r > 0) ? (uint32_t)(p.planes * kept_before(seq_lens, r, p.max_tok, mine)) : 0u;
-  // Each load issues as soon as its address is known (there is no loop here
-  // to hold it up); a skipped piece loads the source base and is not stored.
-  V v[kVpt];
-  int64_t doff[kVpt];
-  bool ok[kVpt];
+  if (!kHostLen && kDir != kPools && (int32_t)lane < r) mine = __builtin_nontemporal_load(seq_lens + lane);
+  int32_t len = kHostLen ? p.n_host : __builtin_amdgcn_readfirstlane(seq_lens[r]);
+  if (!kHostLen && kDir != kPools) asm volatile("" ::"v"(mine));   // keep the load here: not sunk past the exit test
+  len = len < 0 ? 0 : (len > p.max_tok ? p.max_tok : len);
+  const uint32_t n = (uint32_t)len;
+  const uint32_t start = (p.window > 0 && len > p.window) ? (uint32_t)(len - p.window) : 0u;
+  const uint32_t unit0 = p.window > 0 ? fdiv(start, p.unit) : 0u;                        // first unit with a moved token
+  const uint32_t end = n > 0 ? (fdiv(n - 1, p.unit) + 1 - unit0) * p.cpu.d : 0u;         // chunks of this plane
+  if (base >= end) return;                                                               // past this request's tokens
+  const char* const src_base = p.src.base + (int64_t)lz * p.src.layer_stride;
+  char* const dst_base = p.dst.base + (int64_t)lz * p.dst.layer_stride;
+
+  // The packed side: the (plane, token) index of the plane's first moved
+  // token and the bytes of each region of this layer.  False when the request
+  // does not fit and moves whole or not at all; `cut` when its plane does not
+  // fit and moves as far as it does.
+  uint32_t q = 0;
+  int64_t cap = INT64_MAX;
+  bool cut = false;
+  auto packed_side = [&]() -> bool {
+    const uint32_t before = (!kHostLen && r > 0) ? (uint32_t)kept_before(seq_lens, r, p.max_tok, p.window, mine) : 0u;
+    q = (uint32_t)p.planes * before + c * (n - start);
+    const int64_t left = p.total_cap - (int64_t)lz * (kDir == kPack ? p.dst.layer_stride : p.src.layer_stride);
+    cap = left < p.packed_cap ? left : p.packed_cap;
+    cut = (int64_t)(q + (n - start)) * p.region_gran > cap;
+    return !(p.strict && (int64_t)((uint32_t)p.planes * (before + (n - start))) * p.region_gran > cap);
+  };
+  // Chunk j of this lane: its unit, first moved token and granule, the run it
+  // belongs to and its place in that run.
+  struct Piece {
+    uint32_t unit, t, k;
+    int32_t at, run;
+    bool live;
+  };
+  auto piece = [&](uint32_t tile, int j) -> Piece {
+    const uint32_t first = tile + j * kThreads + (kWave ? wave_first : threadIdx.x);
+    Piece a;
+    a.live = first < end;                                     // (kWave: whole spans)
+    const uint32_t rel = a.live ? fdiv(first, p.cpu) : 0u;
+    const uint32_t m = (a.live ? first - rel * p.cpu.d : 0u) + (kWave ? lane : 0u);
+    a.unit = unit0 + rel;
+    const uint32_t f = a.unit * p.unit.d;
+    const uint32_t l = f + p.unit.d < n ? f + p.unit.d : n;
+    a.t = f > start ? f : start;
+    a.k = kHeads ? fdiv(m, p.cpg) : 0u;
+    a.at = (int32_t)((kHeads ? m - a.k * p.cpg.d : m) * 16u);
+    a.run = kHeads ? p.gran : (int32_t)(l - a.t) * p.gran;
+    return a;
+  };
+  // Its run's offset on the packed side, and inside its region.
+  auto packed_byte = [&](const Piece& a, int64_t* in_region) -> int64_t {
+    const int64_t tok = (int64_t)(q + (a.t - start));
+    if (!kHeads) return *in_region = tok * p.gran;
+    const uint32_t sh = fdiv(a.k, p.gps);
+    *in_region = (tok * p.gps.d + (a.k - sh * p.gps.d)) * p.gran;
+    return *in_region + (int64_t)sh * p.packed_cap;
+  };
+  // Per lane: the chunks' table entries first, all in flight together (a
+  // chunk past the end looks up the first unit).
+  int32_t spage[VPT], dpage[VPT];
+  if (!kWave) {
 #pragma unroll
-  for (int j = 0; j < kVpt; ++j) {
-    int64_t soff = 0;
-    doff[j] = 0;
-    ok[j] = false;
-    const uint32_t wbase = base + j * kThreads + wave_first;    // uniform, within plane c
-    if (wbase < end) {
-      const uint32_t t = fdiv(wbase, p.ktp);
-      const uint32_t m = wbase - t * per_tp + lane;
-      const uint32_t k = fdiv(m, p.vpg);
-      const uint32_t e = m - k * p.vpg.d;
-      const Loc at{r, c, t};
-      const uint32_t q2 = q0 + c * (uint32_t)n + t;             // global (request, plane, token) index
-      int64_t so = 0, o = 0;
-      const bool s_ok = p.src.packed ? packed_offset<VB>(p, q2, k, e, &so)
-                                     : pool_offset_wave(p.src, at, k, e * VB, src_pc, &so);
-      const bool d_ok = p.dst.packed ? packed_offset<VB>(p, q2, k, e, &o)
-                                     : pool_offset_wave(p.dst, at, k, e * VB, dst_pc, &o);
-      ok[j] = s_ok & d_ok;
-      soff = ok[j] ? so : 0;
-      doff[j] = o;
+    for (int j = 0; j < VPT; ++j) {
+      const uint32_t idx = base + j * kThreads + threadIdx.x;
+      const uint32_t u = unit0 + (idx < end ? fdiv(idx, p.cpu) : 0u);
+      if (kDir != kUnpack) spage[j] = p.src.tables[(int64_t)r * p.src.bt_stride + fdiv(u, p.src.upp)];
+      if (kDir != kPack) dpage[j] = p.dst.tables[(int64_t)r * p.dst.bt_stride + fdiv(u, p.dst.upp)];
     }
-    v[j] = __builtin_nontemporal_load(reinterpret_cast<const V*>(src_base + soff));
   }
+  // The run's byte of each side; false when its page lies outside the pool.
+  auto source = [&](const Piece& a, int j, int64_t* off) -> bool {
+    if (kDir == kUnpack) {
+      int64_t in_region;
+      *off = packed_byte(a, &in_region);
+      return true;
+    }
+    const uint32_t i = fdiv(a.unit, p.src.upp);
+    const int32_t page = kWave ? page_of_wave(p.src, r, i, src_pc) : spage[j];
+    *off = pool_byte(p.src, c, a.t, a.k, i, page);
+    return page_ok(p.src, page);
+  };
+  auto target = [&](const Piece& a, int j, int64_t* off) -> bool {
+    if (kDir == kPack) {
+      int64_t in_region;
+      *off = packed_byte(a, &in_region);
+      return true;
+    }
+    const uint32_t i = fdiv(a.unit, p.dst.upp);
+    const int32_t page = kWave ? page_of_wave(p.dst, r, i, dst_pc) : dpage[j];
+    *off = pool_byte(p.dst, c, a.t, a.k, i, page);
+    return page_ok(p.dst, page);
+  };
+
+  if (kDir == kUnpack && !packed_side()) return;
+  // Every load, then every store.  No loop or branch sits between the loads:
+  // a lane past its run's end loads the run's last chunk, and a chunk that
+  // does not move that way (past the tokens, an outside page, a short or cut
+  // run) the source's first bytes.  The stores' addresses are worked out
+  // while the loads are in flight, not carried past them: their scalars would
+  // not fit the registers.
+  Chunk16 v[VPT];
+  uint32_t voff[VPT];                                         // the chunk's place in its run
+  uint32_t ok = 0;                                            // bit j: chunk j is a whole vector to store
 #pragma unroll
-  for (int j = 0; j < kVpt; ++j)
-    if (ok[j]) __builtin_nontemporal_store(v[j], reinterpret_cast<V*>(dst_base + doff[j]));
-}
-
-template <int VB, bool kHostLen>
-__global__ __launch_bounds__(kThreads) void kv_reshard_single_kernel(Params p,
-                                                                    const int32_t* __restrict__ seq_lens) {
-  direct_move<VB, false, kHostLen>(p, seq_lens);
-}
-
-template <int VB>
-__global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(Params p,
-                                                                    const int32_t* __restrict__ seq_lens) {
-  direct_move<VB, true>(p, seq_lens);
+  for (int j = 0; j < VPT; ++j) {
+    const Piece a = piece(base, j);
+    int64_t so;
+    const bool in_pool = source(a, j, &so);
+    const bool usable = a.live & in_pool & (a.run >= 16) & !cut;
+    voff[j] = a.run >= 16 ? (uint32_t)(a.at < a.run - 16 ? a.at : a.run - 16) : 0u;
+    ok |= ((usable & (a.at < a.run)) ? 1u : 0u) << j;
+    v[j] = __builtin_nontemporal_load(
+        reinterpret_cast<const Chunk16*>((usable ? src_base + so : p.src.base) + (usable || kDir != kUnpack ? voff[j] : 0u)));
+  }
+  if (kDir == kPack && !packed_side()) return;
+  uint32_t tile = base;
+  asm volatile("" : "+s"(tile));
+  if (!cut) {
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) {
+      const Piece a = piece(tile, j);
+      int64_t o;
+      const bool in_pool = target(a, j, &o);
+      if (in_pool & (ok >> j & 1)) __builtin_nontemporal_store(v[j], reinterpret_cast<Chunk16*>(dst_base + o + voff[j]));
+    }
+  }
+  if (cut | (p.gran < 16 && !kHeads)) {
+#pragma unroll 1
+    for (int j = 0; j < VPT; ++j) {
+      const Piece a = piece(tile, j);
+      int64_t so, o, in_region = 0;
+      const bool s_ok = slow_page<kDir != kUnpack>(p.src, r, c, a.unit, a.t, a.k, &so);
+      const bool d_ok = slow_page<kDir != kPack>(p.dst, r, c, a.unit, a.t, a.k, &o);
+      int32_t run = a.run;
+      if (kDir != kPools) {
+        (kDir == kPack ? o : so) = packed_byte(a, &in_region);
+        if (in_region + run > cap) run = in_region < cap ? (int32_t)(cap - in_region) & -p.grain : 0;
+      }
+      if (a.live && s_ok && d_ok && (cut || a.run < 16) && a.at < run)
+        copy_bytes(dst_base + o + a.at, src_base + so + a.at, run - a.at < 16 ? run - a.at : 16);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -536,25 +669,44 @@ KernelFn kernel_for_mode(int vb) {
 
 KernelFn kernel_for(int vb, bool wave) { return wave ? kernel_for_mode<true>(vb) : kernel_for_mode<false>(vb); }
 
-template <bool kHostLen>
-KernelFn single_kernel_for(int vb) {
-  switch (vb) {
-    case 16: return kv_reshard_single_kernel<16, kHostLen>;
-    case 8: return kv_reshard_single_kernel<8, kHostLen>;
-    case 4: return kv_reshard_single_kernel<4, kHostLen>;
-    case 2: return kv_reshard_single_kernel<2, kHostLen>;
-    default: return kv_reshard_single_kernel<1, kHostLen>;
+template <int kDir, bool kWave, bool kHeads, bool kHostLen>
+KernelFn direct_kernel_vpt(int vpt) {
+  switch (vpt) {
+    case 8: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 8>;
+    case 4: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 4>;
+    case 2: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 2>;
+    default: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 1>;
   }
 }
 
-KernelFn direct_kernel_for(int vb) {
-  switch (vb) {
-    case 16: return kv_reshard_direct_kernel<16>;
-    case 8: return kv_reshard_direct_kernel<8>;
-    case 4: return kv_reshard_direct_kernel<4>;
-    case 2: return kv_reshard_direct_kernel<2>;
-    default: return kv_reshard_direct_kernel<1>;
+template <int kDir>
+KernelFn direct_kernel_dir(bool wave, bool heads, int vpt) {
+  if (heads) return wave ? direct_kernel_vpt<kDir, true, true, false>(vpt) : direct_kernel_vpt<kDir, false, true, false>(vpt);
+  return wave ? direct_kernel_vpt<kDir, true, false, false>(vpt) : direct_kernel_vpt<kDir, false, false, false>(vpt);
+}
+
+// A host length comes from a plain pack or unpack only: whole rows, one packed side.
+template <int kDir>
+KernelFn direct_kernel_host(bool wave, int vpt) {
+  return wave ? direct_kernel_vpt<kDir, true, false, true>(vpt) : direct_kernel_vpt<kDir, false, false, true>(vpt);
+}
+
+KernelFn direct_kernel_for(int dir, bool wave, bool heads, bool host_len, int vpt) {
+  if (host_len) return dir == kPack ? direct_kernel_host<kPack>(wave, vpt) : direct_kernel_host<kUnpack>(wave, vpt);
+  switch (dir) {
+    case kPack: return direct_kernel_dir<kPack>(wave, heads, vpt);
+    case kUnpack: return direct_kernel_dir<kUnpack>(wave, heads, vpt);
+    default: return direct_kernel_dir<kPools>(wave, heads, vpt);
   }
+}
+
+int64_t gcd(int64_t a, int64_t b) {
+  while (b) {
+    const int64_t r = a % b;
+    a = b;
+    b = r;
+  }
+  return a;
 }
 
 // single_only: launch only the one-request direct grid (and report whether it
@@ -567,7 +719,8 @@ KernelFn direct_kernel_for(int vb) {
 topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst, int32_t num_reqs,
                                const int32_t* seq_lens, int32_t head_count, int32_t window,
                                const topkv_launch_t& launch, bool single_only, bool* launched,
-                               int32_t n_host = -1, int32_t layers = 1, int64_t packed_layer_stride = 0) {
+                               int32_t n_host = -1, int32_t layers = 1, int64_t packed_layer_stride = 0,
+                               int64_t total_cap = -1, bool strict = false) {
   *launched = false;
   if (!src || !dst || !valid_layout(src->layout) || !valid_layout(dst->layout)) return TOPKV_ERR_INVALID_ARG;
   if (src->layout == TOPKV_LAYOUT_PACKED && dst->layout == TOPKV_LAYOUT_PACKED) return TOPKV_ERR_INVALID_ARG;
@@ -683,7 +836,7 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
     s.bt_stride = v->bt_stride;
     s.page = make_div((uint32_t)v->pool.page_size);
   }
-  p.packed_cap = packed_cap;
+  p.packed_cap = src->layout == TOPKV_LAYOUT_PACKED || dst->layout == TOPKV_LAYOUT_PACKED ? packed_cap : INT64_MAX;
   p.vpg = make_div((uint32_t)vpg);
   p.gpt = make_div((uint32_t)gpt);
   p.ktp = make_div((uint32_t)(gpt * vpg));
@@ -695,38 +848,85 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
   p.n_host = host_len ? (n_host < max_tok ? n_host : (int32_t)max_tok) : 0;
   p.layers = layers;
 
-  int cus = 0;
-  const topkv_status_t st = cu_count(&cus);
-  if (st != TOPKV_OK) return st;
-  const int64_t tile = (int64_t)kThreads * kVpt;
-  int64_t blocks = (bound + tile - 1) / tile;
-  if (blocks > (int64_t)cus * kWgPerCu) blocks = (int64_t)cus * kWgPerCu;
-  if (blocks < 1) blocks = 1;
-  const size_t lds = sizeof(int32_t) * (kWaves + 3 * (size_t)num_reqs + 1);
-  const bool wave = (gpt * vpg) % 64 == 0;
-  // a host-side length sizes the grid exactly; a device one by the table's capacity
-  const int64_t grid_tok = host_len ? p.n_host : max_tok;
-  const int64_t plane_tiles = (grid_tok * gpt * vpg + tile - 1) / tile;
-  const bool single = TOPKV_RS_SINGLE && num_reqs == 1 && window == 0 && wave && plane_tiles <= INT32_MAX &&
-                      geo->planes <= 65535;
-  // a batch without a window: the same direct grid with requests on z, while it stays within
-  // 2^20 workgroups and 1024 requests (each workgroup sums the lengths before its request)
-  const bool direct = !single && TOPKV_RS_DIRECT && num_reqs > 1 && num_reqs <= 1024 && window == 0 && wave &&
-                      geo->planes <= 65535 && plane_tiles * geo->planes * num_reqs <= ((int64_t)1 << 20);
-  if (single_only && !single) return TOPKV_OK;
-  if (layers > 1 && !((single && layers <= 65535) || (direct && (int64_t)num_reqs * layers <= 65535))) return TOPKV_OK;
-  const dim3 grid = single   ? dim3((unsigned)plane_tiles, (unsigned)geo->planes, (unsigned)layers)
-                    : direct ? dim3((unsigned)plane_tiles, (unsigned)geo->planes, (unsigned)(num_reqs * layers))
-                             : dim3((unsigned)blocks);
-  if (plane_tiles == 0) return TOPKV_OK;   // a host-side length of 0: nothing to move
-  const KernelFn fn = single   ? (host_len ? single_kernel_for<true>(vb) : single_kernel_for<false>(vb))
-                      : direct ? direct_kernel_for(vb)
-                               : kernel_for(vb, wave);
-  const size_t shmem = (single || direct) ? 0 : lds;
+  // Direct grid: units of the most tokens that are one run on both sides.
+  // Whole rows of a slot-major pool are adjacent over a page's slots, and a
+  // packed side's over all tokens.
+  const bool heads = gpt > 1;
+  int64_t unit = 0;
+  for (int i = 0; i < 2; ++i) {
+    const topkv_view_t* v = sides[i];
+    if (v->layout == TOPKV_LAYOUT_PACKED) continue;
+    const bool rows = !heads && head_count == v->pool.num_heads;
+    unit = rows ? gcd(unit, v->pool.page_size) : 1;
+    if (!rows) break;
+  }
+  const int64_t cpg = (gran + 15) / 16;
+  const int64_t cpu = heads ? gpt * cpg : (unit * gran + 15) / 16;
+  const int64_t max_units = (max_tok + unit - 1) / unit;
+  int64_t grid_units = max_units;
+  if (host_len) grid_units = ((int64_t)p.n_host + unit - 1) / unit;
+  else if (window > 0 && ((int64_t)window + unit - 2) / unit + 1 < max_units)
+    grid_units = ((int64_t)window + unit - 2) / unit + 1;   // units that `window` consecutive tokens can touch
+  const bool single = num_reqs == 1;
+  // Chunks are 16 bytes, so a unit's run (a granule's, when it has several)
+  // holds at least one; indices stay below 2^31.
+  const int64_t span = grid_units * cpu, tiles8 = (span + 8 * kThreads - 1) / (8 * kThreads);
+  bool direct = !(host_len && heads) && (heads ? gran : unit * gran) >= 16 && unit * gran <= INT32_MAX - 16 &&
+                span < ((int64_t)1 << 31) - 8 * kThreads && geo->planes <= 65535 && layers <= 65535 &&
+                (src->layout != TOPKV_LAYOUT_PACKED || (packed_cap >= 16 && (total_cap < 0 || total_cap >= 16)));
+  // A batch stays within 2^20 workgroups a layer and 1024 requests (each
+  // workgroup sums the lengths before its request).
+  if (!single)
+    direct = direct && num_reqs <= 1024 && tiles8 * geo->planes * num_reqs <= ((int64_t)1 << 20) &&
+             (int64_t)num_reqs * layers <= 65535;
+  if (direct && grid_units == 0) return TOPKV_OK;             // a host-side length of 0: nothing to move
+  if (!direct && (single_only || layers > 1)) return TOPKV_OK;
+
+  const dim3 threads(kThreads);
+  dim3 grid;
+  size_t lds = 0;
+  KernelFn fn;
+  if (direct) {
+    p.unit = make_div((uint32_t)unit);
+    p.cpu = make_div((uint32_t)cpu);
+    p.cpg = make_div((uint32_t)cpg);
+    p.total_cap = total_cap < 0 ? INT64_MAX : total_cap;
+    p.max_units = (int32_t)max_units;
+    p.gran = (int32_t)gran;
+    p.region_gran = (int32_t)(gpt / shards * gran);
+    p.reqs = make_div((uint32_t)num_reqs);
+    p.grain = vb;
+    p.strict = strict ? 1 : 0;
+    for (int i = 0; i < 2; ++i) {
+      Side& s = i == 0 ? p.src : p.dst;
+      s.upp = make_div(s.packed ? 1u : (uint32_t)(sides[i]->pool.page_size / unit));
+    }
+    // 8 chunks per lane (32 KiB tiles, as the page grids use) while they give
+    // the chip two workgroups per CU; below that, smaller tiles.
+    int vpt = 8;
+    int64_t tiles = tiles8;
+    while (vpt > 1 && tiles * geo->planes * num_reqs * layers < TOPKV_RS_FILL) {
+      vpt >>= 1;
+      tiles = (span + vpt * kThreads - 1) / (vpt * kThreads);
+    }
+    grid = dim3((unsigned)tiles, (unsigned)geo->planes, (unsigned)(single ? layers : num_reqs * layers));
+    const int dir = dst->layout == TOPKV_LAYOUT_PACKED ? kPack : src->layout == TOPKV_LAYOUT_PACKED ? kUnpack : kPools;
+    fn = direct_kernel_for(dir, cpu % 64 == 0, heads, host_len, vpt);
+  } else {
+    int cus = 0;
+    const topkv_status_t st = cu_count(&cus);
+    if (st != TOPKV_OK) return st;
+    const int64_t tile = (int64_t)kThreads * kVpt;
+    int64_t blocks = (bound + tile - 1) / tile;
+    if (blocks > (int64_t)cus * kWgPerCu) blocks = (int64_t)cus * kWgPerCu;
+    grid = dim3((unsigned)(blocks < 1 ? 1 : blocks));
+    lds = sizeof(int32_t) * (kWaves + 3 * (size_t)num_reqs + 1);
+    fn = kernel_for(vb, (gpt * vpg) % 64 == 0);
+  }
   if (launch.start || launch.stop)
-    hipExtLaunchKernelGGL(fn, grid, dim3(kThreads), shmem, launch.stream, launch.start, launch.stop, 0, p, seq_lens);
+    hipExtLaunchKernelGGL(fn, grid, threads, lds, launch.stream, launch.start, launch.stop, 0, p, seq_lens);
   else
-    hipLaunchKernelGGL(fn, grid, dim3(kThreads), shmem, launch.stream, p, seq_lens);
+    hipLaunchKernelGGL(fn, grid, threads, lds, launch.stream, p, seq_lens);
   if (hipGetLastError() != hipSuccess) return TOPKV_ERR_LAUNCH;
   *launched = true;
   return TOPKV_OK;

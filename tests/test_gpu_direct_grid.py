@@ -1,0 +1,139 @@
+"""The layout-move direct grid at the sizes where it can go wrong, bit for bit against the oracle:
+units of several page sizes, wave-uniform and per-lane spans, several granules, rows that are no
+multiple of 16 bytes or shorter than that, windows, each tile size, and packed regions too small."""
+import numpy as np
+import pytest
+import torch
+
+import oracle.reshard as rs
+from gpu_util import say, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+WORDS = {1: np.uint8, 2: np.uint16, 4: np.uint32, 8: np.uint64}
+
+
+@pytest.fixture(scope="module")
+def tk():
+    from paper_2607_28633_amd import topkv
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return topkv
+
+
+def _tables(rng, lens, P):
+    need = [-(-int(n) // P) for n in lens]
+    NP = sum(need) + 3
+    bt = np.full((len(lens), max([1] + need) + 1), -1, dtype=np.int32)
+    perm, cur = rng.permutation(NP).astype(np.int32), 0
+    for r, k in enumerate(need):
+        bt[r, :k] = perm[cur:cur + k]
+        cur += k
+    return bt, NP
+
+
+def _words(rng, n, eb):
+    return rng.integers(0, 256, size=n * eb, dtype=np.uint8).view(WORDS[eb])
+
+
+# heads, dim, elem, P, P2, lengths, head slice (first, count), shards, window
+CASES = [
+    # whole rows: per-lane units (72, 16, 22, 1.5 chunks a token) and wave-uniform ones, tile edges
+    (1, 576, 2, 64, 16, [1, 63, 64, 65, 300], None, 1, 0),
+    (1, 576, 2, 5, 7, [1, 34, 35, 36, 200], None, 1, 0),
+    (1, 128, 2, 16, 1, [15, 16, 17, 511, 512, 513], None, 1, 0),
+    (7, 25, 2, 16, 24, [23, 24, 25, 700], None, 1, 0),
+    (3, 3, 2, 16, 9, [1, 2, 143, 145], None, 1, 0),          # 18-byte rows
+    (1, 6, 1, 16, 4, [1, 2, 3, 63, 64, 65], None, 1, 0),     # 6-byte rows: short last runs
+    (1, 5, 1, 3, 3, [1, 2, 7, 30], None, 1, 0),              # units shorter than a chunk: the general grid
+    (8, 128, 2, 16, 64, [8192], None, 1, 0),                 # 32 KiB tiles, wave-uniform, one request
+    (1, 129, 2, 16, 16, [40000, 1, 39999], None, 1, 0),      # 32 KiB tiles, per lane
+    (8, 128, 2, 16, 16, [2047, 2048, 2049], None, 1, 0),     # 16 KiB tiles
+    (8, 128, 2, 16, 16, [640, 1], None, 1, 0),               # 8 KiB tiles
+    # head slices and shards
+    (8, 128, 2, 16, 16, [100, 1, 33], (2, 2), 1, 0),
+    (8, 128, 2, 16, 64, [100, 1, 33], (0, 8), 4, 0),
+    (6, 20, 2, 8, 16, [50, 9], (1, 4), 2, 0),                # 40-byte granules
+    (6, 9, 1, 8, 16, [50, 9], (1, 4), 2, 0),                 # 18-byte granules
+    # windows
+    (8, 64, 2, 16, 16, [1, 127, 128, 129, 500, 0], None, 1, 128),
+    (1, 576, 2, 64, 16, [1, 100, 101, 164, 500], None, 1, 100),
+    (7, 25, 2, 16, 24, [23, 24, 300, 700], None, 1, 17),
+    (1, 6, 1, 16, 4, [1, 9, 63, 64, 65], None, 1, 5),
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_direct_grid_parity(tk, case):
+    H, D, eb, P, P2, lens, sl, S, W = CASES[case]
+    C, (h0, hc) = 2, sl or (0, H)
+    say(f"[direct_grid] case {case}: H{H} D{D} u{8 * eb} P{P}->{P2} lens {lens} heads {h0}+{hc} shards {S} window {W}")
+    rng = np.random.default_rng(case)
+    lens_h = np.array(lens, dtype=np.int32)
+    (bt, NP), (bt2, NP2) = _tables(rng, lens, P), _tables(rng, lens, P2)
+    src_h = _words(rng, NP * C * P * H * D, eb).reshape(1, NP, C, P, H, D)
+    dst_h = _words(rng, NP2 * C * P2 * H * D, eb).reshape(1, NP2, C, P2, H, D)
+    hm_h = _words(rng, NP2 * C * P2 * H * D, eb).reshape(1, NP2, C, H, P2, D)
+    src, btd, bt2d, lensd, R = to_dev(src_h), to_dev(bt), to_dev(bt2), to_dev(lens_h), len(lens)
+    cap = rs.packed_heads_elems(C, hc // S, D, lens, W)
+    shard = dict(shards=S, shard_elems=cap)
+    pool, to = rs.View(rs.POOL, src_h, 0, bt, h0), lambda kind, d: rs.View(kind, d, 0, bt2, h0)
+    pv = tk.pool_view(src, 0, btd, bt.shape[1], h0)
+
+    want = np.zeros(S * cap, WORDS[eb])
+    rs.move_layer(pool, rs.View(rs.PACKED, want, **shard), lens_h, hc, W)
+    packed = to_dev(np.zeros(S * cap + 16, WORDS[eb]))
+    kv = tk.packed_view(packed, nbytes=cap * eb, shards=S)
+    tk.topkv_move_layer(pv, kv, R, lensd, hc, W)
+    torch.cuda.synchronize()
+    got = to_host(packed)
+    assert np.array_equal(got[:S * cap], want) and not got[S * cap:].any(), "pack"
+
+    for kind, host in ((rs.POOL, dst_h), (rs.POOL_HEAD_MAJOR, hm_h)):
+        dv = lambda d: tk.pool_view(d, 0, bt2d, bt2.shape[1], h0, kind == rs.POOL_HEAD_MAJOR)
+        want_u, dst = host.copy(), to_dev(host)
+        rs.move_layer(rs.View(rs.PACKED, want, **shard), to(kind, want_u), lens_h, hc, W)
+        tk.topkv_move_layer(kv, dv(dst), R, lensd, hc, W)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_host(dst), want_u), f"unpack into {kind}"
+        want_p, dst = host.copy(), to_dev(host)
+        rs.move_layer(pool, to(kind, want_p), lens_h, hc, W)
+        tk.topkv_move_layer(pv, dv(dst), R, lensd, hc, W)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_host(dst), want_p), f"pool to {kind}"
+
+
+@pytest.mark.parametrize("H,D,eb,hc,S", [(8, 128, 2, 8, 1), (7, 25, 2, 7, 1), (8, 128, 2, 4, 2), (1, 6, 1, 1, 1)])
+def test_direct_grid_short_regions(tk, H, D, eb, hc, S):
+    """A packed side too small for the batch: whole pieces below each region's capacity move, nothing past it."""
+    C, P, lens = 2, 16, [33, 5, 70]
+    rng = np.random.default_rng(H + D)
+    bt, NP = _tables(rng, lens, P)
+    src_h = _words(rng, NP * C * P * H * D, eb).reshape(1, NP, C, P, H, D)
+    full = rs.packed_heads_elems(C, hc // S, D, lens)
+    whole = np.zeros(S * full, WORDS[eb])
+    rs.move_layer(rs.View(rs.POOL, src_h, 0, bt, 0), rs.View(rs.PACKED, whole, shards=S, shard_elems=full),
+                  np.array(lens, np.int32), hc)
+    src, btd, lensd = to_dev(src_h), to_dev(bt), to_dev(np.array(lens, np.int32))
+    piece = 16 // eb if (hc // S * D * eb) % 16 == 0 else 2 // eb  # elements of the widest aligned piece of a token
+    for cap in (full - piece, full // 2 // piece * piece, 10 * piece):
+        say(f"[direct_grid] short region H{H} D{D} u{8 * eb} shards {S}: {cap} of {full}")
+        packed = to_dev(np.zeros(S * cap + 16, WORDS[eb]))
+        kv = tk.packed_view(packed, nbytes=cap * eb, shards=S)
+        tk.topkv_move_layer(tk.pool_view(src, 0, btd, bt.shape[1]), kv, 3, lensd, hc)
+        torch.cuda.synchronize()
+        got = to_host(packed)
+        for s in range(S):
+            assert np.array_equal(got[s * cap:(s + 1) * cap], whole[s * full:s * full + cap]), f"shard {s}"
+        assert not got[S * cap:].any()
+        back_h = _words(rng, src_h.size, eb).reshape(src_h.shape)
+        back, want = to_dev(back_h), back_h.copy()
+        tk.topkv_move_layer(kv, tk.pool_view(back, 0, btd, bt.shape[1]), 3, lensd, hc)
+        torch.cuda.synchronize()
+        marks, wide = np.zeros(S * full, WORDS[eb]), np.zeros(S * full, WORDS[eb])
+        for s in range(S):
+            marks[s * full:s * full + cap] = 1
+            wide[s * full:s * full + cap] = whole[s * full:s * full + cap]
+        moved, filled = np.zeros_like(back_h), back_h.copy()
+        shard = dict(shards=S, shard_elems=full)
+        rs.move_layer(rs.View(rs.PACKED, marks, **shard), rs.View(rs.POOL, moved, 0, bt, 0), np.array(lens, np.int32), hc)
+        rs.move_layer(rs.View(rs.PACKED, wide, **shard), rs.View(rs.POOL, filled, 0, bt, 0), np.array(lens, np.int32), hc)
+        assert np.array_equal(to_host(back), np.where(moved == 1, filled, want)), "unpack of a short region"
