@@ -709,16 +709,19 @@ int64_t gcd(int64_t a, int64_t b) {
   return a;
 }
 
-// single_only: launch only the one-request direct grid (and report whether it
-// did through *launched); otherwise whichever grid applies.  layers > 1: the
-// views' layers and the next layers - 1 on grid z of a direct grid (a pool
-// side's layer slabs follow each other; a packed side's layer z starts at
-// data + z * packed_layer_stride), launched only when a direct grid applies:
-// *launched stays false otherwise, with nothing queued.  The caller has
-// checked the layer ranges and the stride.
+// direct_only: launch only the direct grid (and report whether it did through
+// *launched), for a plain pack or unpack whose caller has its own kernels;
+// otherwise whichever grid applies.  layers > 1: the views' layers and the
+// next layers - 1 on grid z of a direct grid (a pool side's layer slabs follow
+// each other; a packed side's layer z starts at data + z *
+// packed_layer_stride), launched only when a direct grid applies: *launched
+// stays false otherwise, with nothing queued.  The caller has checked the
+// layer ranges and the stride.  total_cap >= 0: packed bytes of all layers
+// together; strict: requests that do not fit their layer's packed bytes are
+// not moved (else their pieces that do fit are).
 topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst, int32_t num_reqs,
                                const int32_t* seq_lens, int32_t head_count, int32_t window,
-                               const topkv_launch_t& launch, bool single_only, bool* launched,
+                               const topkv_launch_t& launch, bool direct_only, bool* launched,
                                int32_t n_host = -1, int32_t layers = 1, int64_t packed_layer_stride = 0,
                                int64_t total_cap = -1, bool strict = false) {
   *launched = false;
@@ -726,7 +729,7 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
   if (src->layout == TOPKV_LAYOUT_PACKED && dst->layout == TOPKV_LAYOUT_PACKED) return TOPKV_ERR_INVALID_ARG;
   // a host-side length (n_host >= 0) stands for seq_lens: one request, one-request grid only
   const bool host_len = n_host >= 0;
-  if (host_len && (num_reqs != 1 || !single_only || seq_lens)) return TOPKV_ERR_INVALID_ARG;
+  if (host_len && (num_reqs != 1 || !direct_only || seq_lens)) return TOPKV_ERR_INVALID_ARG;
   if (num_reqs < 0 || head_count <= 0 || window < 0 || (num_reqs > 0 && !seq_lens && !host_len))
     return TOPKV_ERR_INVALID_ARG;
   if (num_reqs > TOPKV_MAX_BATCH_REQS) return TOPKV_ERR_UNSUPPORTED;
@@ -761,7 +764,7 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
   // Checked mode: validate each pool side's tables (an unpack destination for
   // pages named twice), and the packed side's room for every kept token.  The
   // one-request route from a pack/unpack call was checked by its caller.
-  if (!single_only && topkv_internal::checked_mode()) {
+  if (!direct_only && topkv_internal::checked_mode()) {
     const bool has_packed = src->layout == TOPKV_LAYOUT_PACKED || dst->layout == TOPKV_LAYOUT_PACKED;
     const int64_t per_token = (int64_t)geo->planes * (head_count / shards) * geo->head_dim * geo->elem_bytes;
     bool cap_checked = false;
@@ -867,20 +870,18 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
   if (host_len) grid_units = ((int64_t)p.n_host + unit - 1) / unit;
   else if (window > 0 && ((int64_t)window + unit - 2) / unit + 1 < max_units)
     grid_units = ((int64_t)window + unit - 2) / unit + 1;   // units that `window` consecutive tokens can touch
-  const bool single = num_reqs == 1;
   // Chunks are 16 bytes, so a unit's run (a granule's, when it has several)
   // holds at least one; indices stay below 2^31.
   const int64_t span = grid_units * cpu, tiles8 = (span + 8 * kThreads - 1) / (8 * kThreads);
   bool direct = !(host_len && heads) && (heads ? gran : unit * gran) >= 16 && unit * gran <= INT32_MAX - 16 &&
                 span < ((int64_t)1 << 31) - 8 * kThreads && geo->planes <= 65535 && layers <= 65535 &&
                 (src->layout != TOPKV_LAYOUT_PACKED || (packed_cap >= 16 && (total_cap < 0 || total_cap >= 16)));
-  // A batch stays within 2^20 workgroups a layer and 1024 requests (each
-  // workgroup sums the lengths before its request).
-  if (!single)
-    direct = direct && num_reqs <= 1024 && tiles8 * geo->planes * num_reqs <= ((int64_t)1 << 20) &&
-             (int64_t)num_reqs * layers <= 65535;
+  // Within 2^20 workgroups a layer and 1024 requests (each workgroup sums the
+  // lengths before its request).
+  direct = direct && num_reqs <= 1024 && tiles8 * geo->planes * num_reqs <= ((int64_t)1 << 20) &&
+           (int64_t)num_reqs * layers <= 65535;
   if (direct && grid_units == 0) return TOPKV_OK;             // a host-side length of 0: nothing to move
-  if (!direct && (single_only || layers > 1)) return TOPKV_OK;
+  if (!direct && (direct_only || layers > 1)) return TOPKV_OK;
 
   const dim3 threads(kThreads);
   dim3 grid;
@@ -909,7 +910,7 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
       vpt >>= 1;
       tiles = (span + vpt * kThreads - 1) / (vpt * kThreads);
     }
-    grid = dim3((unsigned)tiles, (unsigned)geo->planes, (unsigned)(single ? layers : num_reqs * layers));
+    grid = dim3((unsigned)tiles, (unsigned)geo->planes, (unsigned)(num_reqs * layers));
     const int dir = dst->layout == TOPKV_LAYOUT_PACKED ? kPack : src->layout == TOPKV_LAYOUT_PACKED ? kUnpack : kPools;
     fn = direct_kernel_for(dir, cpu % 64 == 0, heads, host_len, vpt);
   } else {
@@ -1041,17 +1042,16 @@ using namespace topkv_reshard;
 
 namespace topkv_internal {
 
-topkv_status_t single_request_move(bool pack, const topkv_pool_t* pool, int32_t layer, void* packed,
-                                   int64_t packed_cap, const int32_t* tables, int32_t bt_stride,
-                                   const int32_t* seq_lens, int32_t seq_len, const topkv_launch_t* launch,
-                                   bool* launched) {
+topkv_status_t chunk_move(bool pack, const topkv_pool_t* pool, int32_t layer, int32_t layers, void* packed,
+                          int64_t layer_cap, int64_t total_cap, int64_t layer_stride, int32_t num_reqs,
+                          const int32_t* tables, int32_t bt_stride, const int32_t* seq_lens, int32_t seq_len,
+                          int32_t window, const topkv_launch_t* launch, bool* launched) {
   *launched = false;
   const topkv_view_t pv = pool_view(TOPKV_LAYOUT_POOL, pool, layer, tables, bt_stride, 0);
-  const topkv_view_t kv = packed_view(packed, packed_cap, 1);
-  const int32_t n_host = seq_lens ? -1 : seq_len;
+  const topkv_view_t kv = packed_view(packed, layer_cap, 1);
   const topkv_status_t st =
-      pack ? move_layer_impl(&pv, &kv, 1, seq_lens, pool->num_heads, 0, *launch, true, launched, n_host)
-           : move_layer_impl(&kv, &pv, 1, seq_lens, pool->num_heads, 0, *launch, true, launched, n_host);
+      move_layer_impl(pack ? &pv : &kv, pack ? &kv : &pv, num_reqs, seq_lens, pool->num_heads, window, *launch, true,
+                      launched, seq_lens ? -1 : seq_len, layers, layer_stride, total_cap, true);
   // anything this path does not take (limits, shapes) goes back to the caller's kernel
   if (st == TOPKV_ERR_INVALID_ARG || st == TOPKV_ERR_UNSUPPORTED || st == TOPKV_ERR_BOUNDS) {
     *launched = false;

@@ -60,8 +60,8 @@
 #ifndef TOPKV_NT_STORES
 #define TOPKV_NT_STORES TOPKV_NONTEMPORAL
 #endif
-#ifndef TOPKV_ROUTE_SINGLE
-#define TOPKV_ROUTE_SINGLE 1  // one whole-request move with a device length runs the layout-move direct grid
+#ifndef TOPKV_CHUNK_PLANE
+#define TOPKV_CHUNK_PLANE 4096    // page planes below this many bytes take the layout-move direct grid
 #endif
 #ifndef TOPKV_XCD_REMAP
 #define TOPKV_XCD_REMAP 0     // 1: each XCD takes a contiguous eighth of the direct grid (measured slower)
@@ -780,6 +780,23 @@ int narrow_threads(bool direct, int vb, int64_t plane_bytes, int64_t tile) {
   return (int64_t)t * vectors_per_lane(vb, plane_bytes, t) * vb == tile ? t : kThreads;
 }
 
+// Whether a window keeps so small a share of the table that a grid over the
+// table's entries would be mostly slots that exit at once: it keeps at most
+// ceil(window / P) + 1 pages of each request.
+bool sparse_window(int32_t window, int32_t bt_stride, int32_t page_size) {
+  return TOPKV_WINDOW_PERSISTENT && window > 0 &&
+         (((int64_t)window + page_size - 1) / page_size + 1) * 4 <= bt_stride;
+}
+
+// Whether a plain move goes to the layout-move kernel's direct grid.  Its
+// tiles run over the pages of a request where this file's end with a page, so
+// a page plane below 4 KiB (one-token pages, narrow rows) no longer costs a
+// workgroup of its own: 16 requests into one-token pages of two 256-byte
+// heads, 21 MB a layer, 88 -> 11 us a launch.  From 4 KiB on, one page per
+// workgroup needs less index work (16 requests, 4 KiB planes: 5.3 us a launch
+// against 6.5).
+bool takes_chunks(int64_t plane_bytes) { return plane_bytes < TOPKV_CHUNK_PLANE; }
+
 // Shared launcher for the four movement entry points.
 //   pack:     direction (pool -> packed when true)
 //   seq_lens: device lengths (batched) or null (single request of n_single)
@@ -817,24 +834,6 @@ topkv_status_t launch_move(bool pack, const topkv_pool_t* pool, int32_t layer, v
     if (st != TOPKV_OK) return st;
   }
 
-  // One request, every token kept, planes in the packed order: the
-  // layout-move kernel's one-request grid does the same copy with less index
-  // work per piece.  A device length needs a packed buffer large enough for
-  // the whole table (that grid skips pieces past the buffer's end, where this
-  // kernel leaves an overrunning request unmoved); a host length is checked
-  // against the buffer here.
-  const int64_t route_tok = seq_lens ? (int64_t)bt_stride * pool->page_size : n_single;
-  int64_t route_rows, route_bytes;
-  const bool fits = !__builtin_mul_overflow((int64_t)pool->planes, route_tok, &route_rows) &&
-                    !__builtin_mul_overflow(route_rows, g.row_bytes, &route_bytes) && route_bytes <= packed_cap &&
-                    route_tok <= (int64_t)bt_stride * pool->page_size;
-  if (TOPKV_ROUTE_SINGLE && num_reqs == 1 && window == 0 && plane_stride == 0 && layers == 1 && fits) {
-    bool launched = false;
-    st = topkv_internal::single_request_move(pack, pool, layer, packed, packed_cap, tables, bt_stride, seq_lens,
-                                             n_single, launch, &launched);
-    if (st != TOPKV_OK || launched) return st;
-  }
-
   int vb = vector_bytes(reinterpret_cast<uintptr_t>(pool->base), reinterpret_cast<uintptr_t>(packed), g.row_bytes);
   while (plane_stride % vb || layer_stride % vb) vb >>= 1;   // placed planes keep every run vector-aligned
   const int vpt = vectors_per_lane(vb, g.plane_bytes);
@@ -852,15 +851,21 @@ topkv_status_t launch_move(bool pack, const topkv_pool_t* pool, int32_t layer, v
       __builtin_mul_overflow(max_pages, per_page, &work) || work > INT32_MAX || tok_cap > INT32_MAX)
     return TOPKV_ERR_UNSUPPORTED;
 
+  // One request's layer goes there too: a launch of one runs back to back with
+  // the next without the 0.3-0.6 us that this file's grid leaves in between.
+  if (plane_stride == 0 && layers == 1 && ((num_reqs == 1 && window == 0) || takes_chunks(g.plane_bytes))) {
+    bool launched = false;
+    st = topkv_internal::chunk_move(pack, pool, layer, 1, packed, packed_cap, packed_cap, 0, num_reqs, tables, bt_stride,
+                                    seq_lens, n_single, window, launch, &launched);
+    if (st != TOPKV_OK || launched) return st;
+  }
+
   // Direct mapping when every (request, table entry, plane, tile) slot can
   // get its own workgroup; otherwise a persistent grid over the live items.
   const int64_t reqs = seq_lens ? (int64_t)num_reqs : 1;
   const int64_t slots = reqs * bt_stride * per_page;
-  // A window keeps at most ceil(window / P) + 1 pages of each request; when that is a small share of
-  // the table, a direct grid would be mostly slots that exit at once, so the persistent grid (which
-  // visits live items only) takes the launch.
-  const int64_t win_pages = window > 0 ? ((int64_t)window + pool->page_size - 1) / pool->page_size + 1 : bt_stride;
-  const bool sparse = TOPKV_WINDOW_PERSISTENT && seq_lens && win_pages * 4 <= bt_stride;
+  // A sparse window takes the persistent grid, which visits live items only.
+  const bool sparse = seq_lens && sparse_window(window, bt_stride, pool->page_size);
   const bool direct = !sparse && slots <= TOPKV_DIRECT_MAX && bt_stride <= 65535 && reqs <= TOPKV_DIRECT_MAX_REQS;
   dim3 grid3;
   unsigned grid = 0;
@@ -1057,6 +1062,7 @@ topkv_status_t engine_move(bool pack, const topkv_pool_t* pool, int32_t first_la
   if (!waits && work <= TOPKV_DIRECT_MAX && bt_stride <= 65535 && num_reqs <= TOPKV_DIRECT_MAX_REQS &&
       (int64_t)num_reqs * layers <= 65535) {
     const int32_t per = engine_layers_per_grid(layers, layer_stride, opt);
+    const bool chunks = takes_chunks(g.plane_bytes);
     const int threads = narrow_threads(true, vb, g.plane_bytes, tile);
     const void* fn = reinterpret_cast<const void*>(
         pick_kernel(pack, vb, vectors_per_lane(vb, g.plane_bytes, threads), true, true, threads));
@@ -1071,6 +1077,15 @@ topkv_status_t engine_move(bool pack, const topkv_pool_t* pool, int32_t first_la
         q.packed_cap = span;
       char* pool_j = pool_ptr + (int64_t)j * g.layer_bytes;
       char* packed_j = packed_ptr + (int64_t)j * layer_stride;
+      if (chunks) {
+        const topkv_launch_t l = {stream, nullptr, nullptr};
+        bool launched = false;
+        const int64_t layer_cap = layers > 1 && q.packed_cap > layer_stride ? layer_stride : q.packed_cap;
+        st = topkv_internal::chunk_move(pack, pool, first_layer + j, n, packed_j, layer_cap, q.packed_cap, layer_stride,
+                                        num_reqs, tables, bt_stride, seq_lens, 0, 0, &l, &launched);
+        if (st != TOPKV_OK) return st;
+        if (launched) continue;
+      }
       void* args[] = {&pool_j, &packed_j, &tables, &seq_lens, &q};
       const dim3 grid3((unsigned)per_page, (unsigned)bt_stride, (unsigned)(num_reqs * n));
       if (hipLaunchKernel(fn, grid3, dim3(threads), args, (size_t)TOPKV_DIRECT_LDS_PAD, stream) != hipSuccess)

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import oracle.reshard as rs
 from gpu_util import say, to_dev, to_host
 
@@ -137,3 +138,53 @@ def test_direct_grid_short_regions(tk, H, D, eb, hc, S):
         rs.move_layer(rs.View(rs.PACKED, marks, **shard), rs.View(rs.POOL, moved, 0, bt, 0), np.array(lens, np.int32), hc)
         rs.move_layer(rs.View(rs.PACKED, wide, **shard), rs.View(rs.POOL, filled, 0, bt, 0), np.array(lens, np.int32), hc)
         assert np.array_equal(to_host(back), np.where(moved == 1, filled, want)), "unpack of a short region"
+
+
+@pytest.mark.parametrize("H,D,eb,P,P2", [(2, 128, 2, 16, 1), (2, 128, 2, 1, 16), (1, 576, 1, 4, 1), (3, 1, 2, 16, 16),
+                                         (1, 1, 1, 16, 8), (1, 2047, 1, 2, 2), (1, 2048, 1, 2, 2)])
+@pytest.mark.parametrize("short", [False, True])
+def test_small_planes(tk, H, D, eb, P, P2, short):
+    """Page planes below 4 KiB (and one at it) through pack, unpack and the layer engine, with a packed
+    buffer that holds the batch or ends inside the last request, which then does not move at all."""
+    C, L, lens = 2, 3, [1, 0, 40, 515]
+    rng = np.random.default_rng(H + D + P)
+    (bt, NP), (bt2, NP2) = _tables(rng, lens, P), _tables(rng, lens, P2)
+    src_h = _words(rng, L * NP * C * P * H * D, eb).reshape(L, NP, C, P, H, D)
+    dst_h = _words(rng, L * NP2 * C * P2 * H * D, eb).reshape(L, NP2, C, P2, H, D)
+    n = C * H * D * sum(lens)
+    kept = n - C * H * D * lens[-1] if short else n               # elements that move
+    cap = (n - 1) * eb if short else n * eb
+    say(f"[small_planes] H{H} D{D} u{8 * eb} P{P}->{P2} short {short}")
+    src, btd, bt2d, lensd = to_dev(src_h), to_dev(bt), to_dev(bt2), to_dev(np.array(lens, np.int32))
+    used = lens[:-1] + [0] if short else lens
+    packs = [oracle.pack_layer(src_h, l, bt, np.array(used, np.int32)) for l in range(L)]
+    want_dst = dst_h.copy()
+    for l in range(L):
+        oracle.unpack_layer(packs[l], want_dst, l, bt2, np.array(used, np.int32))
+
+    stride = n + 5
+    packed, dst = to_dev(np.zeros(L * stride, WORDS[eb])), to_dev(dst_h)
+    for l in range(L):
+        part = packed[l * stride:(l + 1) * stride]
+        tk.topkv_pack_layer_batched(src, l, len(lens), btd, bt.shape[1], lensd, part, dst_bytes=cap)
+        tk.topkv_unpack_layer_batched(part, dst, l, len(lens), bt2d, bt2.shape[1], lensd, src_bytes=cap)
+    torch.cuda.synchronize()
+    got = to_host(packed).reshape(L, stride)
+    assert all(np.array_equal(got[l][:kept], packs[l]) and not got[l][kept:].any() for l in range(L))
+    assert np.array_equal(to_host(dst), want_dst)
+
+    # the engine: a layer stride one element short of the batch, or a range whose last layer's block is
+    layer = (n - 1) if short else n
+    packed, dst = to_dev(np.zeros(L * n + 16, WORDS[eb])), to_dev(dst_h)
+    tk.topkv_engine_pack_layers(src, 0, L, len(lens), btd, bt.shape[1], lensd, packed, layer * eb,
+                                packed_bytes=((L - 1) * layer + n - (0 if short else 1)) * eb)
+    tk.topkv_engine_unpack_layers(packed, layer * eb, dst, 0, L, len(lens), bt2d, bt2.shape[1], lensd,
+                                  packed_bytes=((L - 1) * layer + n - (0 if short else 1)) * eb)
+    torch.cuda.synchronize()
+    got, want_dst = to_host(packed), dst_h.copy()
+    for l in range(L):
+        whole = not short and l < L - 1
+        part = packs[l] if short or whole else packs[l][:C * H * D * sum(lens[:-1])]
+        assert np.array_equal(got[l * layer:l * layer + part.size], part), f"engine layer {l}"
+        oracle.unpack_layer(part, want_dst, l, bt2, np.array(used if short or whole else lens[:-1] + [0], np.int32))
+    assert np.array_equal(to_host(dst), want_dst)
