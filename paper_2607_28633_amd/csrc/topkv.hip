@@ -853,7 +853,12 @@ topkv_status_t launch_move(bool pack, const topkv_pool_t* pool, int32_t layer, v
 
   // One request's layer goes there too: a launch of one runs back to back with
   // the next without the 0.3-0.6 us that this file's grid leaves in between.
-  if (plane_stride == 0 && layers == 1 && ((num_reqs == 1 && window == 0) || takes_chunks(g.plane_bytes))) {
+  // So does a window that keeps a small share of the table: the chunk grid
+  // spans the window's tokens only, where the page grid has a slot per table
+  // entry.
+  const bool sparse = seq_lens && sparse_window(window, bt_stride, pool->page_size);
+  if (plane_stride == 0 && layers == 1 &&
+      ((num_reqs == 1 && window == 0) || sparse || takes_chunks(g.plane_bytes))) {
     bool launched = false;
     st = topkv_internal::chunk_move(pack, pool, layer, 1, packed, packed_cap, packed_cap, 0, num_reqs, tables, bt_stride,
                                     seq_lens, n_single, window, launch, &launched);
@@ -864,8 +869,8 @@ topkv_status_t launch_move(bool pack, const topkv_pool_t* pool, int32_t layer, v
   // get its own workgroup; otherwise a persistent grid over the live items.
   const int64_t reqs = seq_lens ? (int64_t)num_reqs : 1;
   const int64_t slots = reqs * bt_stride * per_page;
-  // A sparse window takes the persistent grid, which visits live items only.
-  const bool sparse = seq_lens && sparse_window(window, bt_stride, pool->page_size);
+  // A sparse window that the chunk grid does not take runs the persistent
+  // grid, which visits live items only.
   const bool direct = !sparse && slots <= TOPKV_DIRECT_MAX && bt_stride <= 65535 && reqs <= TOPKV_DIRECT_MAX_REQS;
   dim3 grid3;
   unsigned grid = 0;
