@@ -35,6 +35,8 @@ def build_command(out: str = LIBRARY, defines=None, sources=None):
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
            # packed-FP32 instructions are kept out of every kernel
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           # leading scalar kernel arguments arrive in scalar registers instead of being loaded
+           "-mllvm", "-amdgpu-kernarg-preload-count=14",
            "-Wall", f"-I{INCLUDE}", "-o", out]
     for k, v in (defines or {}).items():
         cmd.append(f"-D{k}={v}")

@@ -77,9 +77,9 @@ FastDiv make_div(uint32_t d) {
   return FastDiv{d, (uint32_t)m, s};
 }
 
-__device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv& f) {
-  return (__umulhi(n, f.m) + n) >> f.s;
-}
+__device__ __forceinline__ uint32_t quot(uint32_t n, uint32_t m, uint32_t s) { return (__umulhi(n, m) + n) >> s; }
+
+__device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv& f) { return quot(n, f.m, f.s); }
 
 // One side of a move (kernel argument, by value).
 struct Side {
@@ -110,14 +110,12 @@ struct Params {
   int32_t window;
   int32_t max_tok;          // lengths are clamped to [0, max_tok]
   int32_t n_host;           // one request with a host-side length: its tokens (else unused)
-  int32_t layers;           // direct grids: layers on grid z (1: one layer)
   // direct grids (direct_move):
   FastDiv unit;             // tokens per unit
   FastDiv cpu;              // 16-byte chunks per unit of one plane
   FastDiv cpg;              // 16-byte chunks per granule (kHeads)
   FastDiv reqs;             // requests (grid z is layer * requests + request)
   int64_t total_cap;        // packed bytes from the first layer's region to the end of the last one's
-  int32_t max_units;        // units of a request of max_tok tokens
   int32_t gran;             // bytes of one granule of one token
   int32_t region_gran;      // bytes of one token in a packed region (all its granules)
   int32_t grain;            // a run cut short by the packed capacity is a multiple of this (a power of two)
@@ -351,11 +349,10 @@ __device__ __forceinline__ int32_t kept_before(const int32_t* __restrict__ seq_l
 // take unaligned addresses, so a chunk needs no alignment of its run.
 typedef unsigned int Chunk16 __attribute__((ext_vector_type(4), aligned(1)));
 
-// Page index i of a wave-uniform unit through the scalar cache, the last entry kept.
-__device__ __forceinline__ int32_t page_of_wave(const Side& s, int32_t r, uint32_t i, PageCache& pc) {
+// Entry i of a table row, i wave-uniform, through the scalar cache, the last entry kept.
+__device__ __forceinline__ int32_t page_of_wave(const int32_t* row, uint32_t i, PageCache& pc) {
   if (i != pc.i) {
-    const ConstInt* tab = (const ConstInt*)s.tables;
-    pc.page = __builtin_amdgcn_readfirstlane(tab[(int64_t)r * s.bt_stride + i]);
+    pc.page = __builtin_amdgcn_readfirstlane(((const ConstInt*)row)[i]);
     pc.i = i;
   }
   return pc.page;
@@ -375,12 +372,12 @@ __device__ __forceinline__ int64_t pool_byte(const Side& s, uint32_t c, uint32_t
 // The same with the page looked up, for the byte-by-byte chunks; false for a
 // page outside the pool.
 template <bool kPool>
-__device__ __forceinline__ bool slow_page(const Side& s, int32_t r, uint32_t c, uint32_t unit, uint32_t t, uint32_t k,
-                                          int64_t* off) {
+__device__ __forceinline__ bool slow_page(const Side& s, const int32_t* row, uint32_t c, uint32_t unit, uint32_t t,
+                                          uint32_t k, int64_t* off) {
   *off = 0;
   if (!kPool) return true;
   const uint32_t i = fdiv(unit, s.upp);
-  const int32_t page = s.tables[(int64_t)r * s.bt_stride + i];
+  const int32_t page = row[i];
   *off = pool_byte(s, c, t, k, i, page);
   return page_ok(s, page);
 }
@@ -420,42 +417,76 @@ __device__ __forceinline__ void copy_bytes(char* dst, const char* src, int32_t n
 // re-blocked 64 -> 16 (184 MB) 46.3 -> 36.5 us; and, with sides and lengths
 // as template parameters and the store addresses kept out of the load phase,
 // against the one-request grid before it, one 70B request's layer (33.5 MB)
-// 7.8 -> 7.5 us.
+// 7.8 -> 7.5 us.  With the first table entries and the length loaded together
+// from preloaded arguments, and tiles sized as at max_vpt: 7.5 -> 7.25 us, the
+// head slices 16.9 -> 14.8, the re-block 36.7 -> 35.7, 16 requests into
+// one-token pages of 512 bytes (42 MB) 10.8 -> 9.6 (pack and unpack).
 enum { kPack = 0, kUnpack = 1, kPools = 2 };
 
+// What the table entries and the length are found with comes before Params as
+// 14 dwords of plain arguments, which the hardware preloads into scalar
+// registers: those loads go out next to a wave's loads of Params instead of
+// behind them.  `shifts` holds the shift counts of the
+// divisions by cpu, src.upp, dst.upp and the requests, a byte each.
+constexpr uint32_t kWindowedBit = 1u << 31;                   // in `shifts`: the move has a window
+
 template <int kDir, bool kWave, bool kHeads, bool kHostLen, int VPT>
-__global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(Params p, const int32_t* __restrict__ seq_lens) {
+__global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(
+    const int32_t* __restrict__ src_tables, const int32_t* __restrict__ dst_tables,
+    const int32_t* __restrict__ seq_lens, uint32_t shifts, uint32_t cpu_m, uint32_t src_upp_m, uint32_t dst_upp_m,
+    uint32_t src_stride, uint32_t dst_stride, uint32_t num_reqs, uint32_t reqs_m, Params p) {
   constexpr uint32_t kTile = (uint32_t)kThreads * VPT;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wave_first = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
   const uint32_t c = blockIdx.y;
-  uint32_t lz = 0;
-  int32_t r = 0;
-  if (kHostLen || p.num_reqs == 1) {
-    lz = blockIdx.z;
-  } else if (p.layers > 1) {
-    lz = fdiv(blockIdx.z, p.reqs);
-    r = (int32_t)(blockIdx.z - lz * (uint32_t)p.num_reqs);
-  } else {
-    r = (int32_t)blockIdx.z;
-  }
+  const bool windowed = shifts & kWindowedBit;
+  const uint32_t cpu_s = shifts & 31u, src_upp_s = shifts >> 8 & 31u, dst_upp_s = shifts >> 16 & 31u;
+  const uint32_t lz = kHostLen ? blockIdx.z : quot(blockIdx.z, reqs_m, shifts >> 24 & 31u);
+  const int32_t r = kHostLen ? 0 : (int32_t)(blockIdx.z - lz * num_reqs);
   const uint32_t base = blockIdx.x * kTile;
+  const int32_t* const src_row = kDir != kUnpack ? src_tables + (int64_t)r * src_stride : nullptr;
+  const int32_t* const dst_row = kDir != kPack ? dst_tables + (int64_t)r * dst_stride : nullptr;
+  // Without a window the units are known before the length, so their table
+  // entries load next to it: this wave's first unit, or every lane's (kept
+  // inside the row, whatever the tile; with a window, entries not used).
+  constexpr int kEarly = kWave ? 1 : VPT;
+  uint32_t is[kEarly], id[kEarly];
+#pragma unroll
+  for (int j = 0; j < kEarly; ++j) {
+    const uint32_t u = quot(base + (kWave ? wave_first : j * kThreads + threadIdx.x), cpu_m, cpu_s);
+    is[j] = quot(u, src_upp_m, src_upp_s);
+    id[j] = quot(u, dst_upp_m, dst_upp_s);
+    is[j] = is[j] < src_stride ? is[j] : src_stride - 1;
+    id[j] = id[j] < dst_stride ? id[j] : dst_stride - 1;
+  }
+  const int32_t* const own_len = kHostLen ? nullptr : seq_lens + r;
   PageCache src_pc, dst_pc;
-  if (kWave && p.window == 0) {
-    // the first span's unit is known before the length: prime the page caches
-    const uint32_t u = fdiv(base + wave_first, p.cpu);
-    if (u < (uint32_t)p.max_units) {
-      if (kDir != kUnpack) page_of_wave(p.src, r, fdiv(u, p.src.upp), src_pc);
-      if (kDir != kPack) page_of_wave(p.dst, r, fdiv(u, p.dst.upp), dst_pc);
+  int32_t spage[VPT], dpage[VPT];
+  if (kWave) {
+    src_pc.i = is[0];
+    dst_pc.i = id[0];
+    if (kDir != kUnpack) src_pc.page = __builtin_amdgcn_readfirstlane(((const ConstInt*)src_row)[is[0]]);
+    if (kDir != kPack) dst_pc.page = __builtin_amdgcn_readfirstlane(((const ConstInt*)dst_row)[id[0]]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < kEarly; ++j) {
+      if (kDir != kUnpack) spage[j] = src_row[is[j]];
+      if (kDir != kPack) dpage[j] = dst_row[id[j]];
     }
   }
   // with a batch, each lane below r also loads one earlier request's length
   // (for the request's packed offset) next to this request's own, so the
   // offset costs no memory latency of its own
   int32_t mine = 0;
-  if (!kHostLen && kDir != kPools && (int32_t)lane < r) mine = __builtin_nontemporal_load(seq_lens + lane);
-  int32_t len = kHostLen ? p.n_host : __builtin_amdgcn_readfirstlane(seq_lens[r]);
+  if (!kHostLen && kDir != kPools) mine = __builtin_nontemporal_load(seq_lens + ((int32_t)lane < r ? (int32_t)lane : r));
+  int32_t len = kHostLen ? 0 : __builtin_amdgcn_readfirstlane(*(const ConstInt*)own_len);
+  __builtin_amdgcn_sched_barrier(0);                          // these loads go out before more index arithmetic
+  if (kHostLen) len = p.n_host;
   if (!kHostLen && kDir != kPools) asm volatile("" ::"v"(mine));   // keep the load here: not sunk past the exit test
+  // Every cache line of Params is on its way with the length, not first
+  // touched after the exit test.
+  asm volatile("" ::"s"(p.src.plane_bytes), "s"(p.src.upp.m), "s"(p.dst.page_bytes), "s"(p.packed_cap), "s"(p.gps.m),
+               "s"(p.cpu.m), "s"(p.strict));
   len = len < 0 ? 0 : (len > p.max_tok ? p.max_tok : len);
   const uint32_t n = (uint32_t)len;
   const uint32_t start = (p.window > 0 && len > p.window) ? (uint32_t)(len - p.window) : 0u;
@@ -510,16 +541,15 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(Params p, c
     *in_region = (tok * p.gps.d + (a.k - sh * p.gps.d)) * p.gran;
     return *in_region + (int64_t)sh * p.packed_cap;
   };
-  // Per lane: the chunks' table entries first, all in flight together (a
-  // chunk past the end looks up the first unit).
-  int32_t spage[VPT], dpage[VPT];
-  if (!kWave) {
+  // Per lane, in a window: the chunks' table entries first, all in flight
+  // together (a chunk past the end looks up the first unit).
+  if (!kWave && windowed) {
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
       const uint32_t idx = base + j * kThreads + threadIdx.x;
       const uint32_t u = unit0 + (idx < end ? fdiv(idx, p.cpu) : 0u);
-      if (kDir != kUnpack) spage[j] = p.src.tables[(int64_t)r * p.src.bt_stride + fdiv(u, p.src.upp)];
-      if (kDir != kPack) dpage[j] = p.dst.tables[(int64_t)r * p.dst.bt_stride + fdiv(u, p.dst.upp)];
+      if (kDir != kUnpack) spage[j] = src_row[fdiv(u, p.src.upp)];
+      if (kDir != kPack) dpage[j] = dst_row[fdiv(u, p.dst.upp)];
     }
   }
   // The run's byte of each side; false when its page lies outside the pool.
@@ -530,7 +560,7 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(Params p, c
       return true;
     }
     const uint32_t i = fdiv(a.unit, p.src.upp);
-    const int32_t page = kWave ? page_of_wave(p.src, r, i, src_pc) : spage[j];
+    const int32_t page = kWave ? page_of_wave(src_row, i, src_pc) : spage[j];
     *off = pool_byte(p.src, c, a.t, a.k, i, page);
     return page_ok(p.src, page);
   };
@@ -541,7 +571,7 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(Params p, c
       return true;
     }
     const uint32_t i = fdiv(a.unit, p.dst.upp);
-    const int32_t page = kWave ? page_of_wave(p.dst, r, i, dst_pc) : dpage[j];
+    const int32_t page = kWave ? page_of_wave(dst_row, i, dst_pc) : dpage[j];
     *off = pool_byte(p.dst, c, a.t, a.k, i, page);
     return page_ok(p.dst, page);
   };
@@ -584,8 +614,8 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(Params p, c
     for (int j = 0; j < VPT; ++j) {
       const Piece a = piece(tile, j);
       int64_t so, o, in_region = 0;
-      const bool s_ok = slow_page<kDir != kUnpack>(p.src, r, c, a.unit, a.t, a.k, &so);
-      const bool d_ok = slow_page<kDir != kPack>(p.dst, r, c, a.unit, a.t, a.k, &o);
+      const bool s_ok = slow_page<kDir != kUnpack>(p.src, src_row, c, a.unit, a.t, a.k, &so);
+      const bool d_ok = slow_page<kDir != kPack>(p.dst, dst_row, c, a.unit, a.t, a.k, &o);
       int32_t run = a.run;
       if (kDir != kPools) {
         (kDir == kPack ? o : so) = packed_byte(a, &in_region);
@@ -655,6 +685,8 @@ bool valid_layout(int32_t l) {
 }
 
 typedef void (*KernelFn)(Params, const int32_t*);
+typedef void (*DirectFn)(const int32_t*, const int32_t*, const int32_t*, uint32_t, uint32_t, uint32_t, uint32_t,
+                         uint32_t, uint32_t, uint32_t, uint32_t, Params);
 
 template <bool kWave>
 KernelFn kernel_for_mode(int vb) {
@@ -669,29 +701,44 @@ KernelFn kernel_for_mode(int vb) {
 
 KernelFn kernel_for(int vb, bool wave) { return wave ? kernel_for_mode<true>(vb) : kernel_for_mode<false>(vb); }
 
+// Chunks per lane of a direct grid, at most.  Lanes that find their own units
+// take 2: with 8 each lane's table entries and addresses pile up ahead of its
+// first load (8 requests in slices of two of eight heads, 68 MB a launch:
+// 16.9 us with 8, 15.8 with 4, 14.8 with 2, 18.3 with 1; 350-byte rows, 26 MB:
+// 8.9, 8.1, 7.8 and 9.4).  Whole wave spans take 4 where a span's sides lie
+// scattered over heads or two pools (MLA re-block, 184 MB: 36.4 us with 8,
+// 35.7 with 4, 41.3 with 2; head-major, 270 MB: 102 us, 98.7, 98.8), 8 between a
+// pool and a packed buffer, and up to 16 in windows.
+constexpr int max_vpt(bool wave, bool scattered) { return !wave ? 2 : scattered ? 4 : 16; }
+
 template <int kDir, bool kWave, bool kHeads, bool kHostLen>
-KernelFn direct_kernel_vpt(int vpt) {
+DirectFn direct_kernel_vpt(int vpt) {
+  constexpr int kMax = max_vpt(kWave, kHeads || kDir == kPools);
   switch (vpt) {
-    case 8: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 8>;
-    case 4: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 4>;
+    case 16: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 16) ? 16 : kMax>;
+    case 12: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 12) ? 12 : kMax>;
+    case 8: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 8) ? 8 : kMax>;
+    case 6: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 6) ? 6 : kMax>;
+    case 4: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 4) ? 4 : kMax>;
+    case 3: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 6) ? 3 : kMax>;
     case 2: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 2>;
     default: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 1>;
   }
 }
 
 template <int kDir>
-KernelFn direct_kernel_dir(bool wave, bool heads, int vpt) {
+DirectFn direct_kernel_dir(bool wave, bool heads, int vpt) {
   if (heads) return wave ? direct_kernel_vpt<kDir, true, true, false>(vpt) : direct_kernel_vpt<kDir, false, true, false>(vpt);
   return wave ? direct_kernel_vpt<kDir, true, false, false>(vpt) : direct_kernel_vpt<kDir, false, false, false>(vpt);
 }
 
 // A host length comes from a plain pack or unpack only: whole rows, one packed side.
 template <int kDir>
-KernelFn direct_kernel_host(bool wave, int vpt) {
+DirectFn direct_kernel_host(bool wave, int vpt) {
   return wave ? direct_kernel_vpt<kDir, true, false, true>(vpt) : direct_kernel_vpt<kDir, false, false, true>(vpt);
 }
 
-KernelFn direct_kernel_for(int dir, bool wave, bool heads, bool host_len, int vpt) {
+DirectFn direct_kernel_for(int dir, bool wave, bool heads, bool host_len, int vpt) {
   if (host_len) return dir == kPack ? direct_kernel_host<kPack>(wave, vpt) : direct_kernel_host<kUnpack>(wave, vpt);
   switch (dir) {
     case kPack: return direct_kernel_dir<kPack>(wave, heads, vpt);
@@ -849,7 +896,6 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
   p.window = window;
   p.max_tok = (int32_t)max_tok;
   p.n_host = host_len ? (n_host < max_tok ? n_host : (int32_t)max_tok) : 0;
-  p.layers = layers;
 
   // Direct grid: units of the most tokens that are one run on both sides.
   // Whole rows of a slot-major pool are adjacent over a page's slots, and a
@@ -874,7 +920,7 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
   // holds at least one; indices stay below 2^31.
   const int64_t span = grid_units * cpu, tiles8 = (span + 8 * kThreads - 1) / (8 * kThreads);
   bool direct = !(host_len && heads) && (heads ? gran : unit * gran) >= 16 && unit * gran <= INT32_MAX - 16 &&
-                span < ((int64_t)1 << 31) - 8 * kThreads && geo->planes <= 65535 && layers <= 65535 &&
+                span < ((int64_t)1 << 31) - 16 * kThreads && geo->planes <= 65535 && layers <= 65535 &&
                 (src->layout != TOPKV_LAYOUT_PACKED || (packed_cap >= 16 && (total_cap < 0 || total_cap >= 16)));
   // Within 2^20 workgroups a layer and 1024 requests (each workgroup sums the
   // lengths before its request).
@@ -892,7 +938,6 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
     p.cpu = make_div((uint32_t)cpu);
     p.cpg = make_div((uint32_t)cpg);
     p.total_cap = total_cap < 0 ? INT64_MAX : total_cap;
-    p.max_units = (int32_t)max_units;
     p.gran = (int32_t)gran;
     p.region_gran = (int32_t)(gpt / shards * gran);
     p.reqs = make_div((uint32_t)num_reqs);
@@ -902,17 +947,45 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
       Side& s = i == 0 ? p.src : p.dst;
       s.upp = make_div(s.packed ? 1u : (uint32_t)(sides[i]->pool.page_size / unit));
     }
-    // 8 chunks per lane (32 KiB tiles, as the page grids use) while they give
-    // the chip two workgroups per CU; below that, smaller tiles.
-    int vpt = 8;
-    int64_t tiles = tiles8;
-    while (vpt > 1 && tiles * geo->planes * num_reqs * layers < TOPKV_RS_FILL) {
-      vpt >>= 1;
-      tiles = (span + vpt * kThreads - 1) / (vpt * kThreads);
-    }
-    grid = dim3((unsigned)tiles, (unsigned)geo->planes, (unsigned)(num_reqs * layers));
     const int dir = dst->layout == TOPKV_LAYOUT_PACKED ? kPack : src->layout == TOPKV_LAYOUT_PACKED ? kUnpack : kPools;
-    fn = direct_kernel_for(dir, cpu % 64 == 0, heads, host_len, vpt);
+    const bool wave = cpu % 64 == 0, scattered = heads || dir == kPools;
+    auto workgroups = [&](int v) {
+      return (span + v * kThreads - 1) / (v * kThreads) * geo->planes * num_reqs * layers;
+    };
+    // 8 chunks per lane (32 KiB tiles, as the page grids use) or the most
+    // there may be while they give the chip two workgroups per CU; below that,
+    // smaller tiles.
+    int vpt = wave && !scattered ? 8 : max_vpt(wave, scattered);
+    while (vpt > 1 && workgroups(vpt) < TOPKV_RS_FILL) vpt >>= 1;
+    if (wave && !scattered && window > 0) {
+      // A window's slots are nearly all live, so the grid can fill the chip
+      // evenly: the smallest tiles of at most one workgroup per CU (32
+      // requests' last 128 tokens, 16.8 MB a launch: 5.4 us with 192
+      // workgroups of 48 KiB, 5.7 with 576 of 16 KiB).
+      int cus = 0;
+      const topkv_status_t st = cu_count(&cus);
+      if (st != TOPKV_OK) return st;
+      for (const int v : {1, 2, 3, 4, 6, 8, 12, 16})
+        if (workgroups(v) <= cus) {
+          vpt = v;
+          break;
+        }
+    }
+    const int64_t tiles = (span + vpt * kThreads - 1) / (vpt * kThreads);
+    grid = dim3((unsigned)tiles, (unsigned)geo->planes, (unsigned)(num_reqs * layers));
+    const DirectFn direct_fn = direct_kernel_for(dir, wave, heads, host_len, vpt);
+    const uint32_t shifts = p.cpu.s | p.src.upp.s << 8 | p.dst.upp.s << 16 | p.reqs.s << 24 | (window > 0 ? kWindowedBit : 0u);
+    const int32_t* tables[2] = {p.src.tables, p.dst.tables};
+    uint32_t strides[2] = {(uint32_t)p.src.bt_stride, (uint32_t)p.dst.bt_stride}, requests = (uint32_t)num_reqs;
+    void* args[] = {&tables[0], &tables[1], &seq_lens, const_cast<uint32_t*>(&shifts), &p.cpu.m, &p.src.upp.m, &p.dst.upp.m,
+                    &strides[0], &strides[1], &requests, &p.reqs.m, &p};
+    const void* f = reinterpret_cast<const void*>(direct_fn);
+    const hipError_t e = launch.start || launch.stop
+                             ? hipExtLaunchKernel(f, grid, threads, args, 0, launch.stream, launch.start, launch.stop, 0)
+                             : hipLaunchKernel(f, grid, threads, args, 0, launch.stream);
+    if (e != hipSuccess) return TOPKV_ERR_LAUNCH;
+    *launched = true;
+    return TOPKV_OK;
   } else {
     int cus = 0;
     const topkv_status_t st = cu_count(&cus);

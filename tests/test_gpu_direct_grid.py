@@ -58,6 +58,11 @@ CASES = [
     (8, 64, 2, 16, 16, [1, 127, 128, 129, 500, 0], None, 1, 128),
     (1, 576, 2, 64, 16, [1, 100, 101, 164, 500], None, 1, 100),
     (7, 25, 2, 16, 24, [23, 24, 300, 700], None, 1, 17),
+    # windows of whole wave spans, one workgroup per CU: 3, 6, 12 and 16 chunks per lane
+    (1, 32, 2, 16, 16, [1023 + i for i in range(16)], None, 1, 1024),
+    (1, 32, 2, 16, 16, [1000 + 3 * i for i in range(32)], None, 1, 1024),
+    (1, 32, 2, 16, 16, [990 + 2 * i for i in range(64)], None, 1, 1024),
+    (1, 32, 2, 16, 16, [i if i < 20 else 880 + i for i in range(120)], None, 1, 900),
     (1, 6, 1, 16, 4, [1, 9, 63, 64, 65], None, 1, 5),
 ]
 
