@@ -627,6 +627,77 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(
   }
 }
 
+// One request's plain layer: the direct grid's case of whole rows between a
+// pool and a packed buffer, no window, a row a multiple of 16 bytes and a page
+// plane whole wave spans.  The plane is then one run of 16-byte chunks on the
+// packed side, a span lies in one page, and nothing is left but the page's
+// place.  Lane j of a wave loads the table entry of span j next to the length,
+// one load for all.  The short code lets a lane take up to 16 chunks, so the
+// grid fills the chip in one round of workgroups, or in two.
+// A request that does not fit the packed bytes is not moved; a page outside
+// the pool is not moved (its loads go to page 0, its stores nowhere).
+// Bound: the launch and the chain of entry, data, store below about 8 MB a
+// launch, HBM above.  Against the general direct grid (a unit, a run and a
+// page of its own for each chunk), one 70B layer, us a launch: 1000 tokens
+// (8 MB read and written) 4.0 -> 3.3, 2048 5.0 -> 4.4, 4096 7.2 -> 6.6 (5.1
+// TB/s), 8192 13.9 -> 12.6, 32000 49.0 -> 48.6; one head, 16384 tokens 5.0 -> 4.5.
+struct RowsParams {
+  int64_t page_bytes, plane_bytes;
+  uint32_t num_pages, max_total;   // max_total: chunks of a plane that fit the packed bytes
+  int32_t max_tok;
+};
+
+template <bool kPack, bool kHostLen, int VPT>
+__global__ __launch_bounds__(kThreads) void kv_rows_kernel(char* __restrict__ pool, char* __restrict__ packed,
+                                                           const int32_t* __restrict__ table,
+                                                           const int32_t* __restrict__ seq_lens, int32_t n_host,
+                                                           uint32_t bt_stride, uint32_t per_page, uint32_t per_page_m,
+                                                           uint32_t per_page_s, uint32_t per_token, RowsParams p) {
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t base = blockIdx.x * (kThreads * VPT) + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+  const uint32_t i = quot(base + (lane < VPT ? lane : VPT - 1) * kThreads, per_page_m, per_page_s);
+  const int32_t entries = table[i < bt_stride ? i : bt_stride - 1];
+  int32_t len = kHostLen ? n_host : __builtin_amdgcn_readfirstlane(*(const ConstInt*)seq_lens);
+  asm volatile("" ::"v"(entries), "s"(p.page_bytes), "s"(p.max_total));      // loads of their own are on their way by now
+  len = len < 0 ? 0 : (len > p.max_tok ? p.max_tok : len);
+  const uint32_t total = (uint32_t)len * per_token;                          // chunks of a plane
+  if (base >= total || total > p.max_total) return;
+  char* const pool_plane = pool + (int64_t)blockIdx.y * p.plane_bytes;
+  char* const packed_plane = packed + (int64_t)blockIdx.y * total * 16;
+  // Every load, then every store.  A chunk past the tokens loads the pool's
+  // first ones or the plane's last one, one of a page outside the pool the
+  // pool's first ones.
+  Chunk16 v[VPT];
+  uint32_t ok = 0;
+#pragma unroll
+  for (int j = 0; j < VPT; ++j) {
+    const uint32_t first = base + j * kThreads;
+    const uint32_t entry = (uint32_t)__builtin_amdgcn_readlane(entries, j);
+    const bool usable = (first < total) & (entry < p.num_pages);
+    ok |= (usable ? 1u : 0u) << j;
+    const char* from;
+    if (kPack) {
+      const uint32_t m = first - quot(first, per_page_m, per_page_s) * per_page;
+      from = pool_plane + (usable ? (int64_t)entry * p.page_bytes + (int64_t)m * 16 : 0) + lane * 16u;
+    } else {
+      from = packed_plane + (int64_t)(first + lane < total ? first + lane : total - 1) * 16;
+    }
+    v[j] = __builtin_nontemporal_load(reinterpret_cast<const Chunk16*>(from));
+  }
+#pragma unroll
+  for (int j = 0; j < VPT; ++j) {
+    const uint32_t first = base + j * kThreads;
+    char* to;
+    if (kPack) {
+      to = packed_plane + (int64_t)first * 16 + lane * 16u;
+    } else {
+      const uint32_t m = first - quot(first, per_page_m, per_page_s) * per_page;
+      to = pool_plane + (int64_t)(uint32_t)__builtin_amdgcn_readlane(entries, j) * p.page_bytes + (int64_t)m * 16 + lane * 16u;
+    }
+    if ((ok >> j & 1) && first + lane < total) __builtin_nontemporal_store(v[j], reinterpret_cast<Chunk16*>(to));
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
@@ -745,6 +816,28 @@ DirectFn direct_kernel_for(int dir, bool wave, bool heads, bool host_len, int vp
     case kUnpack: return direct_kernel_dir<kUnpack>(wave, heads, vpt);
     default: return direct_kernel_dir<kPools>(wave, heads, vpt);
   }
+}
+
+typedef void (*RowsFn)(char*, char*, const int32_t*, const int32_t*, int32_t, uint32_t, uint32_t, uint32_t, uint32_t,
+                       uint32_t, RowsParams);
+
+template <bool kPack, bool kHostLen>
+RowsFn rows_kernel_vpt(int vpt) {
+  switch (vpt) {
+    case 16: return kv_rows_kernel<kPack, kHostLen, 16>;
+    case 12: return kv_rows_kernel<kPack, kHostLen, 12>;
+    case 8: return kv_rows_kernel<kPack, kHostLen, 8>;
+    case 6: return kv_rows_kernel<kPack, kHostLen, 6>;
+    case 4: return kv_rows_kernel<kPack, kHostLen, 4>;
+    case 3: return kv_rows_kernel<kPack, kHostLen, 3>;
+    case 2: return kv_rows_kernel<kPack, kHostLen, 2>;
+    default: return kv_rows_kernel<kPack, kHostLen, 1>;
+  }
+}
+
+RowsFn rows_kernel_for(bool pack, bool host_len, int vpt) {
+  if (host_len) return pack ? rows_kernel_vpt<true, true>(vpt) : rows_kernel_vpt<false, true>(vpt);
+  return pack ? rows_kernel_vpt<true, false>(vpt) : rows_kernel_vpt<false, false>(vpt);
 }
 
 int64_t gcd(int64_t a, int64_t b) {
@@ -932,6 +1025,46 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
   const dim3 threads(kThreads);
   dim3 grid;
   size_t lds = 0;
+  const bool to_packed = dst->layout == TOPKV_LAYOUT_PACKED;
+  if (direct && strict && num_reqs == 1 && layers == 1 && window == 0 && !heads && gran % 16 == 0 && cpu % 64 == 0 &&
+      (to_packed || src->layout == TOPKV_LAYOUT_PACKED)) {
+    int cus = 0;
+    const topkv_status_t st = cu_count(&cus);
+    if (st != TOPKV_OK) return st;
+    auto workgroups = [&](int v) { return (span + v * kThreads - 1) / (v * kThreads) * geo->planes; };
+    // The smallest tiles that leave at most one workgroup per CU, or fill most
+    // of two rounds; past that 32 KiB tiles, and 4 KiB ones when the host
+    // knows the length (a table wider than its request costs a workgroup per
+    // tile that is not there).  One 70B layer, us a launch: 4096 tokens 6.5 in
+    // 256 workgroups, 7.6-8.2 in more; 8192 tokens 12.6 in 512, 13.6-14.2 in
+    // more; 32000 tokens 46.4 in 4 KiB tiles, 48.6 in 32 KiB ones; 500 tokens
+    // in a table of 32768 4.3 in 32 KiB tiles, 12.0 in 4 KiB ones.
+    int vpt = host_len ? 1 : 8;
+    for (const int v : {1, 2, 3, 4, 6, 8, 12, 16}) {
+      const int64_t w = workgroups(v);
+      if (w > cus && !(v >= 12 && w <= 2 * cus && w * 10 >= cus * 16)) continue;
+      vpt = v;
+      break;
+    }
+    const Side& ps = to_packed ? p.src : p.dst;
+    char *pool_base = ps.base, *packed_base = to_packed ? p.dst.base : p.src.base;
+    const int32_t* table = ps.tables;
+    FastDiv per_page = make_div((uint32_t)cpu);
+    uint32_t stride = (uint32_t)ps.bt_stride, per_token = (uint32_t)(gran / 16);
+    const int64_t fit = (total_cap >= 0 && total_cap < packed_cap ? total_cap : packed_cap) / 16 / geo->planes;
+    RowsParams q = {ps.page_bytes, ps.plane_bytes, (uint32_t)ps.num_pages, fit < UINT32_MAX ? (uint32_t)fit : UINT32_MAX,
+                    p.max_tok};
+    void* args[] = {&pool_base, &packed_base, &table, &seq_lens, &p.n_host, &stride, &per_page.d, &per_page.m, &per_page.s,
+                    &per_token, &q};
+    const void* f = reinterpret_cast<const void*>(rows_kernel_for(to_packed, host_len, vpt));
+    grid = dim3((unsigned)((span + vpt * kThreads - 1) / (vpt * kThreads)), (unsigned)geo->planes);
+    const hipError_t e = launch.start || launch.stop
+                             ? hipExtLaunchKernel(f, grid, threads, args, 0, launch.stream, launch.start, launch.stop, 0)
+                             : hipLaunchKernel(f, grid, threads, args, 0, launch.stream);
+    if (e != hipSuccess) return TOPKV_ERR_LAUNCH;
+    *launched = true;
+    return TOPKV_OK;
+  }
   KernelFn fn;
   if (direct) {
     p.unit = make_div((uint32_t)unit);

@@ -193,3 +193,49 @@ def test_small_planes(tk, H, D, eb, P, P2, short):
         assert np.array_equal(got[l * layer:l * layer + part.size], part), f"engine layer {l}"
         oracle.unpack_layer(part, want_dst, l, bt2, np.array(used if short or whole else lens[:-1] + [0], np.int32))
     assert np.array_equal(to_host(dst), want_dst)
+
+
+# 64-byte rows in 16-token pages (one wave span a page plane): each tile size of the one-request grid
+ROWS = [1, 15, 16, 17, 1024, 1025, 8192, 8193, 16385, 24577, 32769, 49153, 65537, 98305, 200001, 300000]
+
+
+@pytest.mark.parametrize("n", ROWS)
+def test_one_request_rows(tk, n):
+    H, D, P, P2, C = 1, 32, 16, 32, 2
+    say(f"[direct_grid] one request of {n} tokens")
+    rng = np.random.default_rng(n)
+    lens = np.array([n], dtype=np.int32)
+    (bt, NP), (bt2, NP2) = _tables(rng, lens, P), _tables(rng, lens, P2)
+    bt[0, (n // P) // 2] = NP + 7 if n > 1024 else bt[0, (n // P) // 2]      # a page outside the pool
+    src_h = _words(rng, 2 * NP * C * P * H * D, 2).reshape(2, NP, C, P, H, D)
+    dst_h = _words(rng, 2 * NP2 * C * P2 * H * D, 2).reshape(2, NP2, C, P2, H, D)
+    t = np.arange(n)
+    page = bt[0][t // P]
+    there = page < NP
+    want = np.zeros((C, n, H, D), dtype=np.uint16)
+    want[:, there] = src_h[1][page[there], :, t[there] % P].transpose(1, 0, 2, 3)
+    want_u = dst_h.copy()
+    full = _words(rng, C * n * H * D, 2).reshape(C, n, H, D)
+    want_u[1][bt2[0][t // P2], :, t % P2] = full.transpose(1, 0, 2, 3)
+    src, btd, bt2d, lensd = to_dev(src_h), to_dev(bt), to_dev(bt2), to_dev(lens)
+    size = C * n * H * D
+    wide = torch.full((1, bt.shape[1] * 3), -1, dtype=torch.int32, device="cuda")
+    wide[:, :bt.shape[1]] = btd
+    for table, host_len in ((btd, True), (btd, False), (wide, False)):
+        packed = torch.zeros(size + 8, dtype=torch.int16, device="cuda")
+        dst, body = to_dev(dst_h), to_dev(full.reshape(-1))
+        if host_len:
+            tk.topkv_pack_layer(src, 1, table, n, packed)
+            tk.topkv_unpack_layer(body, dst, 1, bt2d, n)
+        else:
+            tk.topkv_pack_layer_batched(src, 1, 1, table, table.shape[1], lensd, packed, 2 * size)
+            tk.topkv_unpack_layer_batched(body, dst, 1, 1, bt2d, bt2d.shape[1], lensd)
+        torch.cuda.synchronize()
+        got = to_host(packed).view(np.uint16)
+        assert np.array_equal(got[:size].reshape(want.shape), want) and not got[size:].any(), "pack"
+        assert np.array_equal(to_host(dst), want_u), "unpack"
+    packed, dst = torch.zeros(size, dtype=torch.int16, device="cuda"), to_dev(dst_h)
+    tk.topkv_pack_layer_batched(src, 1, 1, btd, bt.shape[1], lensd, packed, 2 * size - 2)
+    tk.topkv_unpack_layer_batched(body, dst, 1, 1, bt2d, bt2d.shape[1], lensd, 2 * size - 2)
+    torch.cuda.synchronize()
+    assert not to_host(packed).any() and np.array_equal(to_host(dst), dst_h), "a request that does not fit moved"
