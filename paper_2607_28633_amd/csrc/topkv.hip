@@ -724,6 +724,8 @@ KernelFn pick_kernel_mode(bool pack, int vb, int vpt) {
       if (vpt == TOPKV_VPT) return kernel_for<16, TOPKV_VPT, kMode>(pack);
       switch (vpt) {
         case 8: return kernel_for<16, 8, kMode>(pack);
+        case 6: return kernel_for<16, 6, kMode>(pack);
+        case 3: return kernel_for<16, 3, kMode>(pack);
         case 4: return kernel_for<16, 4, kMode>(pack);
         case 2: return kernel_for<16, 2, kMode>(pack);
         default: return kernel_for<16, 1, kMode>(pack);
@@ -747,15 +749,22 @@ KernelFn pick_kernel(bool pack, int vb, int vpt, bool direct, bool batched, int 
   return batched ? pick_kernel_mode<kDirectBatched>(pack, vb, vpt) : pick_kernel_mode<kDirectSingle>(pack, vb, vpt);
 }
 
-// Vectors per lane for 16-byte vectors: the largest of TOPKV_VPT, 4, 2, 1
-// whose tile of `threads` lanes still fits in one page plane, so small planes
-// (e.g. 16 KiB for 1 KiB rows in 16-token pages) get full tiles instead of
-// half-empty ones.
+// Vectors per lane for 16-byte vectors: a page plane is cut into as few tiles
+// as TOPKV_VPT allows, and these are made as small as they can be, so that no
+// plane ends in a nearly empty one.  MLA latents (1152-byte rows), against
+// tiles of the largest power of two that fits the plane: 64-token pages (72
+// KiB: 3 tiles of 24 KiB, not 32 + 32 + 8) 32 requests, 8 layers both ways
+// 1342 -> 1319 us; 8-token pages (9 KiB: one tile, not 8 + 1) 9 requests, 28
+// launches 156 -> 118 us.  Planes below 8 KiB run in tiles of 4 KiB
+// (launch_threads).
 int vectors_per_lane(int vb, int64_t plane_bytes, int threads = kThreads) {
   if (vb != 16) return TOPKV_VPT;
-  for (int v = TOPKV_VPT; v > 1; v >>= 1)
-    if ((int64_t)threads * v * 16 <= plane_bytes) return v;
-  return 1;
+  if (plane_bytes < (int64_t)kThreads * 2 * 16) return plane_bytes >= (int64_t)threads * 2 * 16 ? 2 : 1;
+  const int64_t unit = (int64_t)threads * 16;
+  const int64_t tiles = (plane_bytes + unit * TOPKV_VPT - 1) / (unit * TOPKV_VPT);
+  for (const int v : {1, 2, 3, 4, 6})
+    if (v < TOPKV_VPT && tiles * v * unit >= plane_bytes) return v;
+  return TOPKV_VPT;
 }
 
 // Threads per workgroup of a launch.  A direct grid over page planes of 4 to
@@ -945,6 +954,8 @@ EngineFn pick_engine(bool pack, int vb, int vpt) {
     case 16:
       switch (vpt) {
         case 8: return engine_for<16, 8>(pack);
+        case 6: return engine_for<16, 6>(pack);
+        case 3: return engine_for<16, 3>(pack);
         case 4: return engine_for<16, 4>(pack);
         case 2: return engine_for<16, 2>(pack);
         default: return engine_for<16, 1>(pack);

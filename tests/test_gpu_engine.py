@@ -70,6 +70,11 @@ ENGINE_CASES = [
     (dict(name="tiny", num_layers=3, num_heads=3, seq_lens=[64, 48, 33, 17, 1]), 0),     # 6 KiB planes
     (dict(name="tiny", num_layers=3, num_heads=1, head_dim=248, seq_lens=[64, 31, 16]), 0),   # 7.75 KiB
     (dict(name="llama3-70b-tp8", num_layers=5, seq_lens=[4096]), 0),                    # 4 KiB, one request
+    # page planes that are no power of two: 9, 18, 22.5 and 72 KiB (3, 6, 6 and 6 vectors per lane)
+    (dict(name="tiny", num_layers=2, num_heads=1, head_dim=576, page_size=8, seq_lens=[1, 7, 8, 9, 100]), 0),
+    (dict(name="tiny", num_layers=2, num_heads=1, head_dim=576, page_size=16, seq_lens=[15, 16, 17, 100]), 1),
+    (dict(name="tiny", num_layers=2, num_heads=1, head_dim=576, page_size=20, seq_lens=[19, 41, 100]), 0),
+    (dict(name="tiny", num_layers=2, num_heads=1, head_dim=576, page_size=64, seq_lens=[63, 65, 300]), 0),
 ]
 
 
