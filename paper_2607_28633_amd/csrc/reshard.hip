@@ -785,13 +785,17 @@ constexpr int max_vpt(bool wave, bool scattered) { return !wave ? 2 : scattered 
 template <int kDir, bool kWave, bool kHeads, bool kHostLen>
 DirectFn direct_kernel_vpt(int vpt) {
   constexpr int kMax = max_vpt(kWave, kHeads || kDir == kPools);
+  if constexpr (kMax == 16 && !kHostLen) {   // the windows' rule
+    switch (vpt) {
+      case 16: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 16>;
+      case 12: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 12>;
+      case 6: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 6>;
+      case 3: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 3>;
+    }
+  }
   switch (vpt) {
-    case 16: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 16) ? 16 : kMax>;
-    case 12: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 12) ? 12 : kMax>;
     case 8: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 8) ? 8 : kMax>;
-    case 6: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 6) ? 6 : kMax>;
     case 4: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 4) ? 4 : kMax>;
-    case 3: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 6) ? 3 : kMax>;
     case 2: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 2>;
     default: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 1>;
   }

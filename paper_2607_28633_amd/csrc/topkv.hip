@@ -801,13 +801,12 @@ bool sparse_window(int32_t window, int32_t bt_stride, int32_t page_size) {
 // tiles run over the pages of a request where this file's end with a page, so
 // a page plane below 4 KiB (one-token pages, narrow rows) no longer costs a
 // workgroup of its own: 16 requests into one-token pages of two 256-byte
-// heads, 21 MB a layer, 88 -> 11 us a launch.  From 4 KiB on, one page per
+// heads, 21 MB a layer, 88 -> 9.6 us a launch.  From 4 KiB on, one page per
 // workgroup needs less index work (16 requests, 4 KiB planes: 5.3 us a launch
 // against 6.5).
 // Rows or bases that are no multiple of 16 bytes (vb < 16) go there as well:
 // its 16-byte chunks need no alignment, where this file's vectors shrink to 8,
-// 4, 2 or 1 bytes (8 requests of 350-byte rows, 53 MB a pass: 13.3 -> 9.5 us a
-// launch).
+// 4, 2 or 1 bytes (8 requests of 350-byte rows, 26 MB a launch: 13.3 -> 7.9 us).
 bool takes_chunks(int64_t plane_bytes, int vb) { return plane_bytes < TOPKV_CHUNK_PLANE || vb < 16; }
 
 // Shared launcher for the four movement entry points.
