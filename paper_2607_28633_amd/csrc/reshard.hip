@@ -27,9 +27,11 @@
 // needed even where the layout transposes (slot-major <-> head-major).
 // Each lane issues all of its loads before its stores.  Moves of up to 1024
 // requests run a direct grid (kv_reshard_direct_kernel: one workgroup per
-// tile, no prefix scan, any row size); larger batches, and runs of fewer than
-// 16 bytes, a persistent one whose workgroups stride over tiles.  Table
-// entries and lengths are bounds-checked on the device before any access.
+// tile, no prefix scan, any row size) while that is short, and past that the
+// same tiles in a grid that follows the lengths (kv_reshard_live_kernel);
+// larger batches, and runs of fewer than 16 bytes, the general persistent one
+// (kv_reshard_kernel).  Table entries and lengths are bounds-checked on the
+// device before any access.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
@@ -47,6 +49,12 @@ namespace topkv_reshard {
 #ifndef TOPKV_RS_FILL
 #define TOPKV_RS_FILL 512         // direct grids: smaller tiles until there are this many workgroups
 #endif
+#ifndef TOPKV_RS_SLOTS
+#define TOPKV_RS_SLOTS 8192       // direct grids of device lengths: most workgroups; more run the live grid
+#endif
+#ifndef TOPKV_RS_LIVE_PER_CU
+#define TOPKV_RS_LIVE_PER_CU 24   // live grid: workgroups per CU
+#endif
 #ifndef TOPKV_RS_WG_PER_CU
 #define TOPKV_RS_WG_PER_CU 16     // grid cap = CUs * this
 #endif
@@ -55,6 +63,7 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kVpt = TOPKV_RS_VPT;
 constexpr int kWgPerCu = TOPKV_RS_WG_PER_CU;
+constexpr int kLiveVpt = 4;       // live grid: chunks per lane
 
 template <int B> struct Vec;
 template <> struct Vec<16> { typedef unsigned int type __attribute__((ext_vector_type(4))); };
@@ -110,7 +119,7 @@ struct Params {
   int32_t window;
   int32_t max_tok;          // lengths are clamped to [0, max_tok]
   int32_t n_host;           // one request with a host-side length: its tokens (else unused)
-  // direct grids (direct_move):
+  // direct and live grids:
   FastDiv unit;             // tokens per unit
   FastDiv cpu;              // 16-byte chunks per unit of one plane
   FastDiv cpg;              // 16-byte chunks per granule (kHeads)
@@ -327,9 +336,10 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_kernel(Params p, const in
   }
 }
 
-// Kept tokens of requests [0, r): the (plane, token) offset of request r in the packed order is planes times this.  Each wave sums the
-// lengths on its own (lanes stride over them, then a butterfly), so no LDS and
-// no barrier are involved.
+// Kept tokens of requests [0, r): the (plane, token) offset of request r in
+// the packed order is planes times this.  Each wave sums the lengths on its own
+// (lanes stride over them, then a butterfly), so no LDS and no barrier are
+// involved.
 // `mine` is seq_lens[lane] for lanes below r, already loaded by the caller.
 __device__ __forceinline__ int32_t kept_before(const int32_t* __restrict__ seq_lens, int32_t r, int32_t max_tok,
                                                int32_t window, int32_t mine) {
@@ -430,20 +440,29 @@ enum { kPack = 0, kUnpack = 1, kPools = 2 };
 // divisions by cpu, src.upp, dst.upp and the requests, a byte each.
 constexpr uint32_t kWindowedBit = 1u << 31;                   // in `shifts`: the move has a window
 
-template <int kDir, bool kWave, bool kHeads, bool kHostLen, int VPT>
-__global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(
-    const int32_t* __restrict__ src_tables, const int32_t* __restrict__ dst_tables,
-    const int32_t* __restrict__ seq_lens, uint32_t shifts, uint32_t cpu_m, uint32_t src_upp_m, uint32_t dst_upp_m,
-    uint32_t src_stride, uint32_t dst_stride, uint32_t num_reqs, uint32_t reqs_m, Params p) {
+// A tile of the live grid, found from the lengths.
+struct LiveTile {
+  uint32_t lz, c, base, n, before;   // layer, plane, first chunk, request's length, tokens of the requests before it
+  int32_t r;
+};
+
+// One workgroup's tile in either grid: the direct one finds it from blockIdx
+// and its length, the live one brings it.  (By value, as a kernel has them: a
+// reference to Params makes the compiler order its loads differently.)
+template <int kDir, bool kWave, bool kHeads, bool kHostLen, bool kLive, int VPT>
+__device__ __forceinline__ void move_tile(const int32_t* src_tables, const int32_t* dst_tables, const int32_t* seq_lens,
+                                          uint32_t shifts, uint32_t cpu_m, uint32_t src_upp_m, uint32_t dst_upp_m,
+                                          uint32_t src_stride, uint32_t dst_stride, uint32_t num_reqs, uint32_t reqs_m,
+                                          Params p, const LiveTile& live) {
   constexpr uint32_t kTile = (uint32_t)kThreads * VPT;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wave_first = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
-  const uint32_t c = blockIdx.y;
-  const bool windowed = shifts & kWindowedBit;
+  const uint32_t c = kLive ? live.c : blockIdx.y;
+  const bool lookup = kLive || (shifts & kWindowedBit);       // the table entries wait for the length
   const uint32_t cpu_s = shifts & 31u, src_upp_s = shifts >> 8 & 31u, dst_upp_s = shifts >> 16 & 31u;
-  const uint32_t lz = kHostLen ? blockIdx.z : quot(blockIdx.z, reqs_m, shifts >> 24 & 31u);
-  const int32_t r = kHostLen ? 0 : (int32_t)(blockIdx.z - lz * num_reqs);
-  const uint32_t base = blockIdx.x * kTile;
+  const uint32_t lz = kLive ? live.lz : kHostLen ? blockIdx.z : quot(blockIdx.z, reqs_m, shifts >> 24 & 31u);
+  const int32_t r = kLive ? live.r : kHostLen ? 0 : (int32_t)(blockIdx.z - lz * num_reqs);
+  const uint32_t base = kLive ? live.base : blockIdx.x * kTile;
   const int32_t* const src_row = kDir != kUnpack ? src_tables + (int64_t)r * src_stride : nullptr;
   const int32_t* const dst_row = kDir != kPack ? dst_tables + (int64_t)r * dst_stride : nullptr;
   // Without a window the units are known before the length, so their table
@@ -459,10 +478,11 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(
     is[j] = is[j] < src_stride ? is[j] : src_stride - 1;
     id[j] = id[j] < dst_stride ? id[j] : dst_stride - 1;
   }
-  const int32_t* const own_len = kHostLen ? nullptr : seq_lens + r;
+  const int32_t* const own_len = kHostLen || kLive ? nullptr : seq_lens + r;
   PageCache src_pc, dst_pc;
   int32_t spage[VPT], dpage[VPT];
-  if (kWave) {
+  if (kLive) {
+  } else if (kWave) {
     src_pc.i = is[0];
     dst_pc.i = id[0];
     if (kDir != kUnpack) src_pc.page = __builtin_amdgcn_readfirstlane(((const ConstInt*)src_row)[is[0]]);
@@ -478,15 +498,16 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(
   // (for the request's packed offset) next to this request's own, so the
   // offset costs no memory latency of its own
   int32_t mine = 0;
-  if (!kHostLen && kDir != kPools) mine = __builtin_nontemporal_load(seq_lens + ((int32_t)lane < r ? (int32_t)lane : r));
-  int32_t len = kHostLen ? 0 : __builtin_amdgcn_readfirstlane(*(const ConstInt*)own_len);
-  __builtin_amdgcn_sched_barrier(0);                          // these loads go out before more index arithmetic
+  if (!kLive && !kHostLen && kDir != kPools) mine = __builtin_nontemporal_load(seq_lens + ((int32_t)lane < r ? (int32_t)lane : r));
+  int32_t len = kLive ? (int32_t)live.n : kHostLen ? 0 : __builtin_amdgcn_readfirstlane(*(const ConstInt*)own_len);
+  if (!kLive) __builtin_amdgcn_sched_barrier(0);                          // these loads go out before more index arithmetic
   if (kHostLen) len = p.n_host;
-  if (!kHostLen && kDir != kPools) asm volatile("" ::"v"(mine));   // keep the load here: not sunk past the exit test
+  if (!kLive && !kHostLen && kDir != kPools) asm volatile("" ::"v"(mine));   // keep the load here: not sunk past the exit test
   // Every cache line of Params is on its way with the length, not first
   // touched after the exit test.
-  asm volatile("" ::"s"(p.src.plane_bytes), "s"(p.src.upp.m), "s"(p.dst.page_bytes), "s"(p.packed_cap), "s"(p.gps.m),
-               "s"(p.cpu.m), "s"(p.strict));
+  if (!kLive)
+    asm volatile("" ::"s"(p.src.plane_bytes), "s"(p.src.upp.m), "s"(p.dst.page_bytes), "s"(p.packed_cap), "s"(p.gps.m),
+                 "s"(p.cpu.m), "s"(p.strict));
   len = len < 0 ? 0 : (len > p.max_tok ? p.max_tok : len);
   const uint32_t n = (uint32_t)len;
   const uint32_t start = (p.window > 0 && len > p.window) ? (uint32_t)(len - p.window) : 0u;
@@ -504,7 +525,9 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(
   int64_t cap = INT64_MAX;
   bool cut = false;
   auto packed_side = [&]() -> bool {
-    const uint32_t before = (!kHostLen && r > 0) ? (uint32_t)kept_before(seq_lens, r, p.max_tok, p.window, mine) : 0u;
+    const uint32_t before = kLive ? live.before
+                            : (!kHostLen && r > 0) ? (uint32_t)kept_before(seq_lens, r, p.max_tok, p.window, mine)
+                                                   : 0u;
     q = (uint32_t)p.planes * before + c * (n - start);
     const int64_t left = p.total_cap - (int64_t)lz * (kDir == kPack ? p.dst.layer_stride : p.src.layer_stride);
     cap = left < p.packed_cap ? left : p.packed_cap;
@@ -541,9 +564,9 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(
     *in_region = (tok * p.gps.d + (a.k - sh * p.gps.d)) * p.gran;
     return *in_region + (int64_t)sh * p.packed_cap;
   };
-  // Per lane, in a window: the chunks' table entries first, all in flight
-  // together (a chunk past the end looks up the first unit).
-  if (!kWave && windowed) {
+  // Per lane, entries not loaded yet: all in flight together, ahead of the data
+  // (a chunk past the end looks up the first unit).
+  if (!kWave && lookup) {
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
       const uint32_t idx = base + j * kThreads + threadIdx.x;
@@ -624,6 +647,123 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(
       if (a.live && s_ok && d_ok && (cut || a.run < 16) && a.at < run)
         copy_bytes(dst_base + o + a.at, src_base + so + a.at, run - a.at < 16 ? run - a.at : 16);
     }
+  }
+}
+
+template <int kDir, bool kWave, bool kHeads, bool kHostLen, int VPT>
+__global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(
+    const int32_t* __restrict__ src_tables, const int32_t* __restrict__ dst_tables,
+    const int32_t* __restrict__ seq_lens, uint32_t shifts, uint32_t cpu_m, uint32_t src_upp_m, uint32_t dst_upp_m,
+    uint32_t src_stride, uint32_t dst_stride, uint32_t num_reqs, uint32_t reqs_m, Params p) {
+  move_tile<kDir, kWave, kHeads, kHostLen, false, VPT>(src_tables, dst_tables, seq_lens, shifts, cpu_m, src_upp_m, dst_upp_m,
+                                                       src_stride, dst_stride, num_reqs, reqs_m, p, LiveTile{});
+}
+
+// The live grid: the same tiles in a grid that follows the lengths instead of
+// the table's width.  A few workgroups per CU stride over the tiles that have
+// tokens; each scans the lengths once into the requests' live tiles and kept
+// tokens (exclusive prefix sums in LDS) and finds a tile's request with two
+// ballots.  It takes the moves whose direct grid would have more than
+// TOPKV_RS_SLOTS workgroups.
+// A slot past its request's tokens costs the direct grid 0.41 ns, so tables
+// wider than their requests, and batches of uneven ones, would cost more than
+// the data.  us a launch, direct grid -> live grid: slices of two of eight
+// heads, 64 requests of 1000 tokens in tables of 32768 113 -> 25, of 131072
+// 419 -> 25; 128 requests around 512 tokens (sigma 1) in a table that fits the
+// longest 56 -> 35; MLA re-block, 64 x 1000 in 32768 100 -> 29; head-major, the
+// same, 262 -> 91.  Tables that the requests fill are 2 to 10% faster in the
+// direct grid (slices 64 x 1000, 8064 workgroups, 22.8 against 25.2, 256 x 1000
+// 89 against 93; head-major 64 x 1000 88.7 against 90.7, 256 x 1000 (1 GB) 356
+// against 372; 8 layers into one-token pages, 64 x 1000, 183 against 202), but
+// the host doesn't know how full they are.  At the line a launch of dead slots
+// costs the direct grid 3.4 us.
+// 4 chunks per lane: slices 64 x 1000 25.0 us with 2, 24.3 with 4, 24.8 with 8.
+// 24 workgroups per CU: head-major 256 x 1000 391 us with 8, 374 with 16, 372
+// with 24, 369 with 32; each costs a short move its scan (slices, 64 x 100 in a
+// wide table, 5.0 us with 4, 8.2 with 24, 9.7 with 32).
+__device__ void live_prefix(const Params& p, const int32_t* __restrict__ seq_lens, uint32_t tile, int32_t* first,
+                            int32_t* kept, int32_t* lens, uint64_t* wsum) {
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  uint64_t carry = 0;                                         // kept tokens in the high half, tiles in the low one
+  for (int32_t at = 0; at < p.num_reqs; at += kThreads) {
+    const int32_t r = at + (int32_t)threadIdx.x;
+    uint64_t v = 0;
+    if (r < p.num_reqs) {
+      int32_t len = seq_lens[r];
+      len = len < 0 ? 0 : (len > p.max_tok ? p.max_tok : len);
+      lens[r] = len;
+      if (len > 0) {
+        const uint32_t start = (p.window > 0 && len > p.window) ? (uint32_t)(len - p.window) : 0u;
+        const uint32_t units = fdiv((uint32_t)len - 1, p.unit) + 1 - fdiv(start, p.unit);
+        const uint32_t tiles = (units * p.cpu.d + tile - 1) / tile;
+        v = (uint64_t)((uint32_t)len - start) << 32 | (uint32_t)p.planes * tiles;
+      }
+    }
+    uint64_t x = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint64_t y = __shfl_up(x, d, 64);
+      if (lane >= d) x += y;
+    }
+    if (lane == 63) wsum[wave] = x;
+    __syncthreads();
+    uint64_t before = carry, all = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      if (w < wave) before += wsum[w];
+      all += wsum[w];
+    }
+    if (r < p.num_reqs) {
+      first[r] = (int32_t)(uint32_t)(before + x - v);
+      kept[r] = (int32_t)((before + x - v) >> 32);
+    }
+    carry += all;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) first[p.num_reqs] = (int32_t)(uint32_t)carry;
+  __syncthreads();
+}
+
+// The request that tile t < first[num_reqs] belongs to: the last one with
+// first[r] <= t.  A wave tests one request in `step` and then that step's; at
+// most 64 x 64 requests.
+__device__ __forceinline__ int32_t tile_owner(const int32_t* first, int32_t num_reqs, int32_t t) {
+  const int32_t lane = threadIdx.x & 63;
+  const int32_t step = (num_reqs + 63) >> 6;
+  const int32_t a = lane * step;
+  const int32_t group = (__popcll(__ballot(a < num_reqs && first[a < num_reqs ? a : 0] <= t)) - 1) * step;
+  if (step == 1) return group;
+  const int32_t b = group + lane;
+  const bool in = lane < step && b < num_reqs;
+  return group + __popcll(__ballot(in && first[in ? b : 0] <= t)) - 1;
+}
+
+template <int kDir, bool kWave, bool kHeads>
+__global__ __launch_bounds__(kThreads) void kv_reshard_live_kernel(const int32_t* __restrict__ src_tables,
+                                                                   const int32_t* __restrict__ dst_tables,
+                                                                   const int32_t* __restrict__ seq_lens, uint32_t layers,
+                                                                   Params p) {
+  constexpr uint32_t kTile = (uint32_t)kThreads * kLiveVpt;
+  extern __shared__ uint64_t lds_u64[];
+  int32_t* const first = reinterpret_cast<int32_t*>(lds_u64 + kWaves);   // [num_reqs + 1]
+  int32_t* const kept = first + p.num_reqs + 1;                          // [num_reqs]
+  int32_t* const lens = kept + p.num_reqs;                               // [num_reqs]
+  live_prefix(p, seq_lens, kTile, first, kept, lens, lds_u64);
+  const uint32_t per_layer = (uint32_t)__builtin_amdgcn_readfirstlane(first[p.num_reqs]);
+  const uint32_t all = per_layer * layers;                               // the host keeps this below 2^31
+  for (uint32_t w = blockIdx.x; w < all; w += gridDim.x) {
+    const uint32_t lz = w / per_layer;
+    const uint32_t t = w - lz * per_layer;
+    const int32_t r = __builtin_amdgcn_readfirstlane(tile_owner(first, p.num_reqs, (int32_t)t));
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane(lens[r]);
+    const uint32_t before = (uint32_t)__builtin_amdgcn_readfirstlane(kept[r]);
+    const uint32_t local = t - (uint32_t)__builtin_amdgcn_readfirstlane(first[r]);
+    const uint32_t tiles = (uint32_t)__builtin_amdgcn_readfirstlane(first[r + 1] - first[r]) / (uint32_t)p.planes;
+    const uint32_t c = local / tiles;
+    move_tile<kDir, kWave, kHeads, false, true, kLiveVpt>(src_tables, dst_tables, seq_lens, 0, 0, 0, 0,
+                                                          (uint32_t)p.src.bt_stride, (uint32_t)p.dst.bt_stride, 0, 0, p,
+                                                          LiveTile{lz, c, (local - c * tiles) * kTile, n, before, r});
   }
 }
 
@@ -822,6 +962,22 @@ DirectFn direct_kernel_for(int dir, bool wave, bool heads, bool host_len, int vp
   }
 }
 
+typedef void (*LiveFn)(const int32_t*, const int32_t*, const int32_t*, uint32_t, Params);
+
+template <int kDir>
+LiveFn live_kernel_dir(bool wave, bool heads) {
+  if (heads) return wave ? kv_reshard_live_kernel<kDir, true, true> : kv_reshard_live_kernel<kDir, false, true>;
+  return wave ? kv_reshard_live_kernel<kDir, true, false> : kv_reshard_live_kernel<kDir, false, false>;
+}
+
+LiveFn live_kernel_for(int dir, bool wave, bool heads) {
+  switch (dir) {
+    case kPack: return live_kernel_dir<kPack>(wave, heads);
+    case kUnpack: return live_kernel_dir<kUnpack>(wave, heads);
+    default: return live_kernel_dir<kPools>(wave, heads);
+  }
+}
+
 typedef void (*RowsFn)(char*, char*, const int32_t*, const int32_t*, int32_t, uint32_t, uint32_t, uint32_t, uint32_t,
                        uint32_t, RowsParams);
 
@@ -1015,14 +1171,13 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
     grid_units = ((int64_t)window + unit - 2) / unit + 1;   // units that `window` consecutive tokens can touch
   // Chunks are 16 bytes, so a unit's run (a granule's, when it has several)
   // holds at least one; indices stay below 2^31.
-  const int64_t span = grid_units * cpu, tiles8 = (span + 8 * kThreads - 1) / (8 * kThreads);
+  const int64_t span = grid_units * cpu;
   bool direct = !(host_len && heads) && (heads ? gran : unit * gran) >= 16 && unit * gran <= INT32_MAX - 16 &&
                 span < ((int64_t)1 << 31) - 16 * kThreads && geo->planes <= 65535 && layers <= 65535 &&
                 (src->layout != TOPKV_LAYOUT_PACKED || (packed_cap >= 16 && (total_cap < 0 || total_cap >= 16)));
-  // Within 2^20 workgroups a layer and 1024 requests (each workgroup sums the
-  // lengths before its request).
-  direct = direct && num_reqs <= 1024 && tiles8 * geo->planes * num_reqs <= ((int64_t)1 << 20) &&
-           (int64_t)num_reqs * layers <= 65535;
+  // Up to 1024 requests: each workgroup of the direct grid sums the lengths
+  // before its request, each of the live grid holds all of them in LDS.
+  direct = direct && num_reqs <= 1024 && (int64_t)num_reqs * layers <= 65535;
   if (direct && grid_units == 0) return TOPKV_OK;             // a host-side length of 0: nothing to move
   if (!direct && (direct_only || layers > 1)) return TOPKV_OK;
 
@@ -1107,6 +1262,24 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
           vpt = v;
           break;
         }
+    }
+    if (!host_len && workgroups(vpt) > TOPKV_RS_SLOTS) {
+      if (layers > 1 && workgroups(kLiveVpt) > INT32_MAX) return TOPKV_OK;   // the caller moves one layer per launch
+      int cus = 0;
+      const topkv_status_t st = cu_count(&cus);
+      if (st != TOPKV_OK) return st;
+      const int64_t most = (int64_t)cus * TOPKV_RS_LIVE_PER_CU;
+      grid = dim3((unsigned)(workgroups(kLiveVpt) < most ? workgroups(kLiveVpt) : most));
+      lds = sizeof(uint64_t) * kWaves + sizeof(int32_t) * (3 * (size_t)num_reqs + 1);
+      uint32_t count = (uint32_t)layers;
+      void* args[] = {&p.src.tables, &p.dst.tables, &seq_lens, &count, &p};
+      const void* f = reinterpret_cast<const void*>(live_kernel_for(dir, wave, heads));
+      const hipError_t e = launch.start || launch.stop
+                               ? hipExtLaunchKernel(f, grid, threads, args, lds, launch.stream, launch.start, launch.stop, 0)
+                               : hipLaunchKernel(f, grid, threads, args, lds, launch.stream);
+      if (e != hipSuccess) return TOPKV_ERR_LAUNCH;
+      *launched = true;
+      return TOPKV_OK;
     }
     const int64_t tiles = (span + vpt * kThreads - 1) / (vpt * kThreads);
     grid = dim3((unsigned)tiles, (unsigned)geo->planes, (unsigned)(num_reqs * layers));

@@ -255,3 +255,53 @@ def test_strict_moves_whole_requests():
         assert model_move(Side(rs.POOL, pool, 0, bt), Side(rs.PACKED, out), lens, 3, 0, cap, 1, 1, 1, strict=True)
         whole = max([0] + [2 * row * x for x in (7, 16, 19) if 2 * row * x <= cap])
         assert np.array_equal(out[:whole], want[:whole]) and (out[whole:] == 7).all()
+
+
+def _live_tiles(lens, planes, unit, cpu, window, max_tok, tile):
+    """live_prefix: each request's live tiles over all planes and kept tokens, as exclusive prefix sums."""
+    d_unit, first, kept, clamped = make_div(unit), [0], [0], []
+    for n in lens:
+        n = min(max(int(n), 0), max_tok)
+        clamped.append(n)
+        start = n - window if 0 < window < n else 0
+        units = int(fdiv(n - 1, d_unit)) + 1 - int(fdiv(start, d_unit)) if n > 0 else 0
+        first.append(first[-1] + planes * -(-units * cpu // tile))
+        kept.append(kept[-1] + n - start)
+    return first, kept[:-1], clamped
+
+
+def _tile_owner(first, R, t):
+    """tile_owner: two rounds of 64 lanes' votes."""
+    step = (R + 63) >> 6
+    group = (sum(lane * step < R and first[lane * step if lane * step < R else 0] <= t for lane in range(64)) - 1) * step
+    if step == 1:
+        return group
+    return group + sum(lane < step and group + lane < R and first[group + lane] <= t for lane in range(64)) - 1
+
+
+@pytest.mark.parametrize("R", [1, 2, 63, 64, 65, 127, 128, 129, 200, 1000, 1024])
+def test_live_grid_visits_every_tile_once(R):
+    """The grid that follows the lengths: its tile indices name every (request, plane, tile) with tokens
+    once, with the packed offset of the direct grid's sum, whatever requests are empty."""
+    rng = random.Random(R)
+    for trial in range(6):
+        planes, unit, cpu, tile = rng.choice([1, 2, 3]), rng.choice([1, 7, 16, 64]), rng.choice([1, 22, 64, 72]), 256 * rng.choice([2, 4, 8])
+        window, max_tok = rng.choice([0, 0, 100]), 3000
+        share = [0.0, 0.1, 0.9, 1.0][trial % 4]                     # of empty or negative lengths
+        lens = [rng.choice([0, -1]) if rng.random() < share else rng.choice([1, rng.randint(1, 300), 4000]) for _ in range(R)]
+        if trial == 5:
+            lens = [0] * (R - 1) + [17]
+        first, kept, clamped = _live_tiles(lens, planes, unit, cpu, window, max_tok, tile)
+        want = []
+        for r, n in enumerate(clamped):
+            start = n - window if 0 < window < n else 0
+            end = ((n - 1) // unit + 1 - start // unit) * cpu if n else 0
+            want += [(r, c, x) for c in range(planes) for x in range(-(-end // tile))]
+            assert kept[r] == sum(min(k, window) if window else k for k in clamped[:r])
+        got = []
+        for t in range(first[R]):
+            r = _tile_owner(first, R, t)
+            tiles = (first[r + 1] - first[r]) // planes
+            local = t - first[r]
+            got.append((r, local // tiles, local % tiles))
+        assert got == want

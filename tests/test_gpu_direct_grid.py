@@ -1,6 +1,9 @@
-"""The layout-move direct grid at the sizes where it can go wrong, bit for bit against the oracle:
-units of several page sizes, wave-uniform and per-lane spans, several granules, rows that are no
-multiple of 16 bytes or shorter than that, windows, each tile size, and packed regions too small."""
+"""The layout-move direct and live grids at the sizes where they can go wrong, bit for bit against the
+oracle: units of several page sizes, wave-uniform and per-lane spans, several granules, rows that are no
+multiple of 16 bytes or shorter than that, windows, each tile size, packed regions too small, and block
+tables much wider than their requests."""
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -239,3 +242,89 @@ def test_one_request_rows(tk, n):
     tk.topkv_unpack_layer_batched(body, dst, 1, 1, bt2d, bt2d.shape[1], lensd, 2 * size - 2)
     torch.cuda.synchronize()
     assert not to_host(packed).any() and np.array_equal(to_host(dst), dst_h), "a request that does not fit moved"
+
+
+DIRECT_SLOTS = 8192                                          # most workgroups of a direct grid of device lengths
+# windows whose grid is longer than that although most requests are short
+WIDE_WINDOWS = [(1, 576, 2, 64, 16, [2, 0, 3100, 150, 64, 65] * 10, None, 1, 3000),
+                (7, 25, 2, 16, 24, [9, 2300, 0, 1, 8, 33] * 10, None, 1, 2000),
+                (8, 128, 2, 16, 64, [9, 300, 0, 1, 8, 33] * 10, (2, 2), 1, 2000)]
+
+
+def _wide(row, R, C):
+    """Tokens of a table whose direct grid is past DIRECT_SLOTS in its largest (2048-chunk) tiles."""
+    return -(-(DIRECT_SLOTS + 1) // (R * C)) * 2048 * 16 // row + 2048
+
+
+@pytest.mark.parametrize("case", [i for i, c in enumerate(CASES) if not c[8]] + [len(CASES) + i for i in range(len(WIDE_WINDOWS))])
+def test_wide_tables(tk, case, monkeypatch):
+    """Every kind of move with block tables much wider than the requests (entries past them hold anything):
+    the live grid."""
+    H, D, eb, P, P2, lens, sl, S, W = (CASES + WIDE_WINDOWS)[case]
+    hc, narrow, R = (sl or (0, H))[1], _tables, len(lens)
+    wide = 0 if W else min(_wide(hc * D * eb, R, 2), (1 << 31) // (R * 2 * hc * D * eb) - 64)
+
+    def tables(rng, lens, page):
+        bt, NP = narrow(rng, lens, page)
+        out = rng.integers(-(1 << 31), 1 << 31, size=(R, max(bt.shape[1], wide // page)), dtype=np.int64).astype(np.int32)
+        out[:, :bt.shape[1]] = np.where(bt < 0, out[:, :bt.shape[1]], bt)
+        return out, NP
+    monkeypatch.setattr(sys.modules[__name__], "_tables", tables)
+    monkeypatch.setattr(sys.modules[__name__], "CASES", CASES + WIDE_WINDOWS)
+    test_direct_grid_parity(tk, case)
+
+
+@pytest.mark.parametrize("short", [False, True])
+def test_small_planes_in_wide_tables(tk, short, monkeypatch):
+    """Plain layers and the layer engine over small page planes, with tables that put them in the live grid."""
+    narrow = _tables
+
+    def tables(rng, lens, page):
+        bt, NP = narrow(rng, lens, page)
+        return np.concatenate([bt, np.full((len(lens), 40000 // page), -1, np.int32)], axis=1), NP
+    monkeypatch.setattr(sys.modules[__name__], "_tables", tables)
+    test_small_planes(tk, 2, 128, 2, 16, 1, short)
+    test_small_planes(tk, 2, 128, 2, 1, 16, short)
+
+
+def _us(call, n=30):
+    for _ in range(3):
+        call()
+    best = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(n):
+            call()
+        b.record()
+        b.synchronize()
+        best.append(a.elapsed_time(b) * 1000 / n)
+    return sorted(best)[2]
+
+
+@pytest.mark.parametrize("kind", ["slice", "reblock", "tokens"])
+def test_table_width_costs_little(tk, kind):
+    """64 requests of 100 tokens in tables of 131072 tokens: the launch follows the lengths (about 2 times
+    the exact tables' launch), where a grid over the tables' entries takes 40 to 100 times it."""
+    R, n, C = 64, 100, 2
+    H, D, P, P2 = {"slice": (8, 128, 16, 16), "reblock": (1, 576, 64, 16), "tokens": (2, 128, 16, 1)}[kind]
+    rng = np.random.default_rng(1)
+    (bt, NP), (bt2, NP2) = _tables(rng, [n] * R, P), _tables(rng, [n] * R, P2)
+    src = torch.zeros((1, NP, C, P, H, D), dtype=torch.int16, device="cuda")
+    dst = torch.zeros((1, NP2, C, P2, H, D), dtype=torch.int16, device="cuda")
+    packed = torch.zeros(C * R * n * H * D, dtype=torch.int16, device="cuda")
+    lens = to_dev(np.full(R, n, np.int32))
+    us = {}
+    for width in (n, 131072):
+        t, t2 = (to_dev(np.pad(b, ((0, 0), (0, max(0, width // p - b.shape[1]))), constant_values=-1)) for b, p in ((bt, P), (bt2, P2)))
+        say(f"[direct_grid] {kind}: tables {tuple(t.shape)} and {tuple(t2.shape)}")
+        if kind == "slice":
+            call = tk.prepare_pack_layer_heads(src, 0, R, t, t.shape[1], lens, 2, 2, packed)
+        elif kind == "reblock":
+            call = tk.prepare_move_layer(tk.pool_view(src, 0, t, t.shape[1]), tk.pool_view(dst, 0, t2, t2.shape[1]), R, lens, H)
+        else:
+            call = tk.prepare_unpack_layer_window(packed, dst, 0, R, t2, t2.shape[1], lens, 0)
+        us[width] = _us(call)
+        torch.cuda.synchronize()
+    say(f"[direct_grid] {kind}: {us}")
+    assert us[131072] < 8 * us[n]
