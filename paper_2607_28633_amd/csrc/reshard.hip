@@ -398,6 +398,12 @@ __device__ __forceinline__ void copy_bytes(char* dst, const char* src, int32_t n
 
 // Direct grid: workgroup (x, y, z) copies tile x of plane y of request z (of
 // layer z / num_reqs when several layers go out in one grid), in packed order.
+// With a window x and z change places: the first tiles of every request come
+// first.  A window's grid is as long as the window for each request, and where
+// requests are shorter than it only their first tiles have tokens; with a
+// request's tiles side by side those recur every so many workgroups, and the
+// round-robin dispatch gives them to few CUs (24 requests of 200 tokens of 1 KiB
+// in windows of 1000: 10.0 -> 5.3 us a launch).
 // A request's plane is cut into units: the most tokens that are one
 // contiguous run on both sides (the smaller side's page, or what divides both
 // page sizes, when whole rows move; one token when heads are sliced or laid
@@ -458,11 +464,13 @@ __device__ __forceinline__ void move_tile(const int32_t* src_tables, const int32
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wave_first = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
   const uint32_t c = kLive ? live.c : blockIdx.y;
-  const bool lookup = kLive || (shifts & kWindowedBit);       // the table entries wait for the length
+  const bool windowed = !kHostLen && (shifts & kWindowedBit);
+  const bool lookup = kLive || windowed;                      // the table entries wait for the length
+  const uint32_t block_z = windowed ? blockIdx.x : blockIdx.z, block_x = windowed ? blockIdx.z : blockIdx.x;
   const uint32_t cpu_s = shifts & 31u, src_upp_s = shifts >> 8 & 31u, dst_upp_s = shifts >> 16 & 31u;
-  const uint32_t lz = kLive ? live.lz : kHostLen ? blockIdx.z : quot(blockIdx.z, reqs_m, shifts >> 24 & 31u);
-  const int32_t r = kLive ? live.r : kHostLen ? 0 : (int32_t)(blockIdx.z - lz * num_reqs);
-  const uint32_t base = kLive ? live.base : blockIdx.x * kTile;
+  const uint32_t lz = kLive ? live.lz : kHostLen ? block_z : quot(block_z, reqs_m, shifts >> 24 & 31u);
+  const int32_t r = kLive ? live.r : kHostLen ? 0 : (int32_t)(block_z - lz * num_reqs);
+  const uint32_t base = kLive ? live.base : block_x * kTile;
   const int32_t* const src_row = kDir != kUnpack ? src_tables + (int64_t)r * src_stride : nullptr;
   const int32_t* const dst_row = kDir != kPack ? dst_tables + (int64_t)r * dst_stride : nullptr;
   // Without a window the units are known before the length, so their table
@@ -918,21 +926,13 @@ KernelFn kernel_for(int vb, bool wave) { return wave ? kernel_for_mode<true>(vb)
 // 16.9 us with 8, 15.8 with 4, 14.8 with 2, 18.3 with 1; 350-byte rows, 26 MB:
 // 8.9, 8.1, 7.8 and 9.4).  Whole wave spans take 4 where a span's sides lie
 // scattered over heads or two pools (MLA re-block, 184 MB: 36.4 us with 8,
-// 35.7 with 4, 41.3 with 2; head-major, 270 MB: 102 us, 98.7, 98.8), 8 between a
-// pool and a packed buffer, and up to 16 in windows.
-constexpr int max_vpt(bool wave, bool scattered) { return !wave ? 2 : scattered ? 4 : 16; }
+// 35.7 with 4, 41.3 with 2; head-major, 270 MB: 102 us, 98.7, 98.8), and 8 (32
+// KiB tiles, as the page grids use) between a pool and a packed buffer.
+constexpr int max_vpt(bool wave, bool scattered) { return !wave ? 2 : scattered ? 4 : 8; }
 
 template <int kDir, bool kWave, bool kHeads, bool kHostLen>
 DirectFn direct_kernel_vpt(int vpt) {
   constexpr int kMax = max_vpt(kWave, kHeads || kDir == kPools);
-  if constexpr (kMax == 16 && !kHostLen) {   // the windows' rule
-    switch (vpt) {
-      case 16: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 16>;
-      case 12: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 12>;
-      case 6: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 6>;
-      case 3: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, 3>;
-    }
-  }
   switch (vpt) {
     case 8: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 8) ? 8 : kMax>;
     case 4: return kv_reshard_direct_kernel<kDir, kWave, kHeads, kHostLen, (kMax >= 4) ? 4 : kMax>;
@@ -1172,7 +1172,7 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
   // Chunks are 16 bytes, so a unit's run (a granule's, when it has several)
   // holds at least one; indices stay below 2^31.
   const int64_t span = grid_units * cpu;
-  bool direct = !(host_len && heads) && (heads ? gran : unit * gran) >= 16 && unit * gran <= INT32_MAX - 16 &&
+  bool direct = !(host_len && (heads || window > 0)) && (heads ? gran : unit * gran) >= 16 && unit * gran <= INT32_MAX - 16 &&
                 span < ((int64_t)1 << 31) - 16 * kThreads && geo->planes <= 65535 && layers <= 65535 &&
                 (src->layout != TOPKV_LAYOUT_PACKED || (packed_cap >= 16 && (total_cap < 0 || total_cap >= 16)));
   // Up to 1024 requests: each workgroup of the direct grid sums the lengths
@@ -1244,25 +1244,10 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
     auto workgroups = [&](int v) {
       return (span + v * kThreads - 1) / (v * kThreads) * geo->planes * num_reqs * layers;
     };
-    // 8 chunks per lane (32 KiB tiles, as the page grids use) or the most
-    // there may be while they give the chip two workgroups per CU; below that,
-    // smaller tiles.
-    int vpt = wave && !scattered ? 8 : max_vpt(wave, scattered);
+    // The most chunks per lane there may be while they give the chip two
+    // workgroups per CU; below that, smaller tiles.
+    int vpt = max_vpt(wave, scattered);
     while (vpt > 1 && workgroups(vpt) < TOPKV_RS_FILL) vpt >>= 1;
-    if (wave && !scattered && window > 0) {
-      // A window's slots are nearly all live, so the grid can fill the chip
-      // evenly: the smallest tiles of at most one workgroup per CU (32
-      // requests' last 128 tokens, 16.8 MB a launch: 5.4 us with 192
-      // workgroups of 48 KiB, 5.7 with 576 of 16 KiB).
-      int cus = 0;
-      const topkv_status_t st = cu_count(&cus);
-      if (st != TOPKV_OK) return st;
-      for (const int v : {1, 2, 3, 4, 6, 8, 12, 16})
-        if (workgroups(v) <= cus) {
-          vpt = v;
-          break;
-        }
-    }
     if (!host_len && workgroups(vpt) > TOPKV_RS_SLOTS) {
       if (layers > 1 && workgroups(kLiveVpt) > INT32_MAX) return TOPKV_OK;   // the caller moves one layer per launch
       int cus = 0;
@@ -1283,6 +1268,7 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
     }
     const int64_t tiles = (span + vpt * kThreads - 1) / (vpt * kThreads);
     grid = dim3((unsigned)tiles, (unsigned)geo->planes, (unsigned)(num_reqs * layers));
+    if (window > 0) grid = dim3(grid.z, grid.y, grid.x);      // at most TOPKV_RS_SLOTS tiles: no host length here
     const DirectFn direct_fn = direct_kernel_for(dir, wave, heads, host_len, vpt);
     const uint32_t shifts = p.cpu.s | p.src.upp.s << 8 | p.dst.upp.s << 16 | p.reqs.s << 24 | (window > 0 ? kWindowedBit : 0u);
     const int32_t* tables[2] = {p.src.tables, p.dst.tables};

@@ -46,7 +46,10 @@
 #define TOPKV_DIRECT_MAX (1 << 20)  // largest one-shot direct-mapped grid (slots)
 #endif
 #ifndef TOPKV_WINDOW_PERSISTENT
-#define TOPKV_WINDOW_PERSISTENT 1   // windows that keep a small share of the table take the persistent grid
+#define TOPKV_WINDOW_PERSISTENT 1   // windows that keep a small share of the table leave the direct page grid
+#endif
+#ifndef TOPKV_CHUNK_WINDOW
+#define TOPKV_CHUNK_WINDOW (32ll << 20)  // of those: largest window capacity that the layout-move direct grid takes
 #endif
 #ifndef TOPKV_DIRECT_MAX_REQS
 #define TOPKV_DIRECT_MAX_REQS 1024  // direct grid: each slot sums the lengths of the requests before its own
@@ -797,6 +800,20 @@ bool sparse_window(int32_t window, int32_t bt_stride, int32_t page_size) {
          (((int64_t)window + page_size - 1) / page_size + 1) * 4 <= bt_stride;
 }
 
+// Whether a sparse window goes to the layout-move kernel's direct grid, which
+// has a slot for every token of every window, instead of the persistent grid,
+// which scans the lengths and visits live pages only.  By the packed bytes of
+// full windows, chunk grid against persistent grid (rows of 1 to 2 KiB, windows
+// of 128 to 1000, requests longer and shorter than the window): up to 8 MB 0.67
+// to 0.90 of its time, 16 MB 0.73 to 1.05, 32 MB 0.66 to 1.05; 64 MB 0.68 to
+// 1.29, 90 MB and more 0.8 to 1.2, on average slower (32 requests' last 128
+// tokens, 8.4 MB: 6.4 -> 4.5 us a launch).
+bool window_takes_chunks(int64_t num_reqs, int32_t planes, int32_t window, int64_t row_bytes) {
+  int64_t bytes;
+  return !__builtin_mul_overflow(num_reqs * planes, (int64_t)window, &bytes) &&
+         !__builtin_mul_overflow(bytes, row_bytes, &bytes) && bytes <= TOPKV_CHUNK_WINDOW;
+}
+
 // Whether a plain move goes to the layout-move kernel's direct grid.  Its
 // tiles run over the pages of a request where this file's end with a page, so
 // a page plane below 4 KiB (one-token pages, narrow rows) no longer costs a
@@ -865,12 +882,12 @@ topkv_status_t launch_move(bool pack, const topkv_pool_t* pool, int32_t layer, v
 
   // One request's layer goes there too: a launch of one runs back to back with
   // the next without the 0.3-0.6 us that this file's grid leaves in between.
-  // So does a window that keeps a small share of the table: the chunk grid
-  // spans the window's tokens only, where the page grid has a slot per table
-  // entry.
+  // So does a small window of a wide table: the chunk grid spans the window's
+  // tokens only, where the page grid has a slot per table entry.
   const bool sparse = seq_lens && sparse_window(window, bt_stride, pool->page_size);
   if (plane_stride == 0 && layers == 1 &&
-      ((num_reqs == 1 && window == 0) || sparse || takes_chunks(g.plane_bytes, vb))) {
+      ((num_reqs == 1 && window == 0) || takes_chunks(g.plane_bytes, vb) ||
+       (sparse && window_takes_chunks(num_reqs, pool->planes, window, g.row_bytes)))) {
     bool launched = false;
     st = topkv_internal::chunk_move(pack, pool, layer, 1, packed, packed_cap, packed_cap, 0, num_reqs, tables, bt_stride,
                                     seq_lens, n_single, window, launch, &launched);

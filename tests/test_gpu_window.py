@@ -102,3 +102,66 @@ def test_gpt_oss_fullsize(tk):
             say(f"  layer {layer} W={W}: {nb} B bit-exact vs oracle")
     del src, dst, packed, again
     torch.cuda.empty_cache()
+
+
+def _sparse(rng, lens, H, D, P, width):
+    """A pool and tables `width` tokens wide of requests of these lengths."""
+    need = [-(-int(n) // P) for n in lens]
+    bt = np.full((len(lens), width // P), -1, dtype=np.int32)
+    perm, at = rng.permutation(sum(need) + 3).astype(np.int32), 0
+    for r, k in enumerate(need):
+        bt[r, :k] = perm[at:at + k]
+        at += k
+    return bt, (1, sum(need) + 3, 2, P, H, D)
+
+
+@pytest.mark.parametrize("R,W,P,P2", [(16, 1024, 16, 16), (17, 1024, 16, 16), (31, 500, 16, 48), (40, 500, 16, 16)])
+def test_sparse_windows(tk, R, W, P, P2):
+    """Windows of wide tables on both sides of 32 MiB of window capacity (1 KiB rows, two planes), over requests
+    that are mostly shorter than the window."""
+    H, D = 8, 64
+    rng = np.random.default_rng(R + W)
+    lens = np.array([[200, 0, 1, W - 1, W, W + 1, 37, 1500][r % 8] for r in range(R)], dtype=np.int32)
+    (bt, shape), (bt2, shape2) = _sparse(rng, lens, H, D, P, 32768), _sparse(rng, lens, H, D, P2, 32768)
+    src_h, dst_h = (rng.integers(0, 65536, size=s, dtype=np.uint16) for s in (shape, shape2))
+    say(f"[window] sparse: {R} requests, window {W}, pages {P}->{P2}")
+    want, want_dst = oracle.pack_layer(src_h, 0, bt, lens, window=W), dst_h.copy()
+    oracle.unpack_layer(want, want_dst, 0, bt2, lens, window=W)
+    src, dst, btd, bt2d, lensd = to_dev(src_h), to_dev(dst_h), to_dev(bt), to_dev(bt2), to_dev(lens)
+    packed = to_dev(np.zeros(want.size + 16, np.uint16))
+    tk.topkv_pack_layer_window(src, 0, R, btd, bt.shape[1], lensd, W, packed, dst_bytes=2 * want.size)
+    tk.topkv_unpack_layer_window(packed, dst, 0, R, bt2d, bt2.shape[1], lensd, W, src_bytes=2 * want.size)
+    torch.cuda.synchronize()
+    got = to_host(packed)
+    assert np.array_equal(got[:want.size], want) and not got[want.size:].any()
+    assert np.array_equal(to_host(dst), want_dst)
+
+
+@pytest.mark.parametrize("R", [24, 300])
+def test_short_requests_in_windows(tk, R):
+    """Requests of 200 tokens in windows of 1000 move in about the time that they take without a window, in
+    tables as wide as they are (1.6 and 2.4 times it where the live tiles share few CUs)."""
+    H, D, P, n = 8, 64, 16, 200
+    rng = np.random.default_rng(R)
+    bt, shape = _sparse(rng, [n] * R, H, D, P, 32768)
+    src = torch.zeros(shape, dtype=torch.int16, device="cuda")
+    packed = torch.zeros(2 * R * n * H * D, dtype=torch.int16, device="cuda")
+    lens, wide = to_dev(np.full(R, n, np.int32)), to_dev(bt)
+    exact = to_dev(np.ascontiguousarray(bt[:, :-(-n // P)]))
+    say(f"[window] short requests: {R}")
+    windowed = tk.prepare_pack_layer_window(src, 0, R, wide, wide.shape[1], lens, 1000, packed)
+    plain = tk.prepare_pack_layer_window(src, 0, R, exact, exact.shape[1], lens, 0, packed)
+    us = []
+    for call in (windowed, plain) * 5:
+        for _ in range(3):
+            call()
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(30):
+            call()
+        b.record()
+        b.synchronize()
+        us.append(a.elapsed_time(b) * 1000 / 30)
+    windowed_us, plain_us = sorted(us[::2])[2], sorted(us[1::2])[2]
+    say(f"[window] {R} requests of {n} tokens: window {windowed_us:.2f} us, plain {plain_us:.2f} us")
+    assert windowed_us < 1.5 * plain_us + 1.0
