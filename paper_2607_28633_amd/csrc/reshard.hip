@@ -402,8 +402,8 @@ __device__ __forceinline__ void copy_bytes(char* dst, const char* src, int32_t n
 // first.  A window's grid is as long as the window for each request, and where
 // requests are shorter than it only their first tiles have tokens; with a
 // request's tiles side by side those recur every so many workgroups, and the
-// round-robin dispatch gives them to few CUs (24 requests of 200 tokens of 1 KiB
-// in windows of 1000: 10.0 -> 5.3 us a launch).
+// round-robin dispatch gives them to few CUs (16 requests of 200 tokens of 1 KiB
+// in windows of 1000: 7.5 -> 4.3 us a launch).
 // A request's plane is cut into units: the most tokens that are one
 // contiguous run on both sides (the smaller side's page, or what divides both
 // page sizes, when whole rows move; one token when heads are sliced or laid
