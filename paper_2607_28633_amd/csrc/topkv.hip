@@ -752,22 +752,30 @@ KernelFn pick_kernel(bool pack, int vb, int vpt, bool direct, bool batched, int 
   return batched ? pick_kernel_mode<kDirectBatched>(pack, vb, vpt) : pick_kernel_mode<kDirectSingle>(pack, vb, vpt);
 }
 
-// Vectors per lane for 16-byte vectors: a page plane is cut into as few tiles
-// as TOPKV_VPT allows, and these are made as small as they can be, so that no
-// plane ends in a nearly empty one.  MLA latents (1152-byte rows), against
-// tiles of the largest power of two that fits the plane: 64-token pages (72
-// KiB: 3 tiles of 24 KiB, not 32 + 32 + 8) 32 requests, 8 layers both ways
-// 1342 -> 1319 us; 8-token pages (9 KiB: one tile, not 8 + 1) 9 requests, 28
-// launches 156 -> 118 us.  Planes below 8 KiB run in tiles of 4 KiB
-// (launch_threads).
+// Vectors per lane for 16-byte vectors.  Planes below 8 KiB run in tiles of 4
+// KiB (launch_threads); others in tiles of the largest power of two that fits
+// the plane, at most TOPKV_VPT vectors a lane, with two exceptions:
+//   * a plane of more than 3/4 of the largest tile is one such tile (28 KiB:
+//     one tile, not 16 + 12; 14 KiB in one of 16 instead of 8 + 6 is slower,
+//     15.5 -> 17.5 us);
+//   * a plane whose last tile would be so empty that the tiles span more than
+//     4/3 of the plane is cut in tiles of 3/4 of the next size instead
+//     (9 KiB: one of 12, not 8 + 1; 40 KiB: 24 + 16, not 32 + 8).
+// Time against the powers of two alone, batches of 8 x 4096 to 300 x 64 tokens:
+// planes of 9 KiB 0.72, 11.5 KiB 0.94, 20 KiB 0.74, 23 KiB 0.80, 28 KiB 0.91, 36
+// KiB 0.83, 47 KiB 0.83, 66 KiB 0.80, 70 KiB 0.86; but at exactly 4/3 the same
+// tiles lose: 12 KiB 1.06, 24 KiB 0.99, 48 KiB 1.04, 72 KiB 0.99 to 1.04, and MLA's
+// 72 KiB in windows (128 x 4096, last 1000) 1.10.
 int vectors_per_lane(int vb, int64_t plane_bytes, int threads = kThreads) {
   if (vb != 16) return TOPKV_VPT;
   if (plane_bytes < (int64_t)kThreads * 2 * 16) return plane_bytes >= (int64_t)threads * 2 * 16 ? 2 : 1;
   const int64_t unit = (int64_t)threads * 16;
-  const int64_t tiles = (plane_bytes + unit * TOPKV_VPT - 1) / (unit * TOPKV_VPT);
-  for (const int v : {1, 2, 3, 4, 6})
-    if (v < TOPKV_VPT && tiles * v * unit >= plane_bytes) return v;
-  return TOPKV_VPT;
+  int v = TOPKV_VPT;
+  while (v > 2 && v * unit > plane_bytes) v >>= 1;
+  if (v * 2 == TOPKV_VPT && plane_bytes * 2 > v * unit * 3) return TOPKV_VPT;
+  const int64_t tiles = (plane_bytes + v * unit - 1) / (v * unit);
+  if (tiles * v * unit * 3 > plane_bytes * 4) return v == TOPKV_VPT ? v * 3 / 4 : v * 3 / 2;
+  return v;
 }
 
 // Threads per workgroup of a launch.  A direct grid over page planes of 4 to

@@ -525,3 +525,50 @@ def test_widest_table(tk):
     with pytest.raises(tk.TopkvError) as ei:
         tk.topkv_pack_layer_batched(src, 0, 1, bt[0], width + 1, lens[0:1], packed, dst_bytes=2 * size)
     assert ei.value.status == tk.TOPKV_ERR_UNSUPPORTED
+
+
+# page planes at which the page grids change their tiles (1, 2, 3, 4, 6 or 8 vectors a lane, one to three tiles)
+PLANES = [7936, 8192, 8448, 12032, 12288, 12544, 16384, 16640, 24320, 24576, 24832, 32768, 33024, 48896, 49152, 49408,
+          65792, 73472, 73728, 73984]
+
+
+@pytest.mark.parametrize("plane", PLANES)
+@pytest.mark.parametrize("R", [3, 1030], ids=["direct", "persistent"])
+def test_plane_tiles(tk, plane, R):
+    """Plain layers and the layer engine over page planes on both sides of every change of tile size, with full
+    and partial pages; more than 1024 requests run the persistent grids."""
+    P, C, L = 16, 2, 2
+    row = plane // P
+    rng = np.random.default_rng(plane + R)
+    lens = np.array([[17, 2 * P, 5][r % 3] if R == 3 else [1, P - 1, 0][r % 3] for r in range(R)], dtype=np.int32)
+    need = [-(-int(n) // P) for n in lens]
+    bt, NP = np.full((R, max(need)), -1, dtype=np.int32), sum(need)
+    perm, at = rng.permutation(NP).astype(np.int32), 0
+    for r, k in enumerate(need):
+        bt[r, :k] = perm[at:at + k]
+        at += k
+    shape = (L, NP, C, P, 1, row)
+    say(f"[plane_tiles] planes of {plane} bytes, {R} requests")
+    src_h = rng.integers(0, 256, size=shape, dtype=np.uint8)
+    want = [oracle.pack_layer(src_h, l, bt, lens) for l in range(L)]
+    n = want[0].size
+    src, btd, lensd = to_dev(src_h), to_dev(bt), to_dev(lens)
+    want_dst = np.zeros(shape, np.uint8)
+    for l in range(L):
+        oracle.unpack_layer(want[l], want_dst, l, bt, lens)
+    packed, dst = torch.zeros((L, n + 16), dtype=torch.uint8, device="cuda"), torch.zeros(shape, dtype=torch.uint8, device="cuda")
+    for l in range(L):
+        part = packed[l, :n]
+        tk.topkv_pack_layer_batched(src, l, R, btd, bt.shape[1], lensd, part)
+        tk.topkv_unpack_layer_batched(part, dst, l, R, btd, bt.shape[1], lensd)
+    torch.cuda.synchronize()
+    got = to_host(packed)
+    assert all(np.array_equal(got[l, :n], want[l]) and not got[l, n:].any() for l in range(L))
+    assert np.array_equal(to_host(dst), want_dst)
+    packed, dst = torch.zeros(L * n + 16, dtype=torch.uint8, device="cuda"), torch.zeros(shape, dtype=torch.uint8, device="cuda")
+    tk.topkv_engine_pack_layers(src, 0, L, R, btd, bt.shape[1], lensd, packed, n, packed_bytes=L * n)
+    tk.topkv_engine_unpack_layers(packed, n, dst, 0, L, R, btd, bt.shape[1], lensd, packed_bytes=L * n)
+    torch.cuda.synchronize()
+    got = to_host(packed)
+    assert np.array_equal(got[:L * n], np.concatenate(want)) and not got[L * n:].any()
+    assert np.array_equal(to_host(dst), want_dst)
