@@ -1192,13 +1192,15 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
     if (st != TOPKV_OK) return st;
     auto workgroups = [&](int v) { return (span + v * kThreads - 1) / (v * kThreads) * geo->planes; };
     // The smallest tiles that leave at most one workgroup per CU, or fill most
-    // of two rounds; past that 32 KiB tiles, and 4 KiB ones when the host
-    // knows the length (a table wider than its request costs a workgroup per
+    // of two rounds; past that 32 KiB tiles (24 KiB ones while they make three
+    // rounds, where 32 KiB make a little more than two), and 4 KiB ones when the
+    // host knows the length (a table wider than its request costs a workgroup per
     // tile that is not there).  One 70B layer, us a launch: 4096 tokens 6.5 in
-    // 256 workgroups, 7.6-8.2 in more; 8192 tokens 12.6 in 512, 13.6-14.2 in
-    // more; 32000 tokens 46.4 in 4 KiB tiles, 48.6 in 32 KiB ones; 500 tokens
-    // in a table of 32768 4.3 in 32 KiB tiles, 12.0 in 4 KiB ones.
-    int vpt = host_len ? 1 : 8;
+    // 256 workgroups, 7.6-8.2 in more; 4200 tokens 8.2 in 32 KiB tiles, 7.5 in 24
+    // KiB ones; 8192 tokens 12.6 in 512 workgroups, 13.6-14.2 in more; 32000
+    // tokens 46.4 in 4 KiB tiles, 48.6 in 32 KiB ones; 500 tokens in a table of
+    // 32768 4.3 in 32 KiB tiles, 12.0 in 4 KiB ones.
+    int vpt = host_len ? 1 : workgroups(6) <= 3 * (int64_t)cus ? 6 : 8;
     for (const int v : {1, 2, 3, 4, 6, 8, 12, 16}) {
       const int64_t w = workgroups(v);
       if (w > cus && !(v >= 12 && w <= 2 * cus && w * 10 >= cus * 16)) continue;

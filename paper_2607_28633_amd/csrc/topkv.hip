@@ -834,6 +834,13 @@ bool window_takes_chunks(int64_t num_reqs, int32_t planes, int32_t window, int64
 // 4, 2 or 1 bytes (8 requests of 350-byte rows, 26 MB a launch: 13.3 -> 7.9 us).
 bool takes_chunks(int64_t plane_bytes, int vb) { return plane_bytes < TOPKV_CHUNK_PLANE || vb < 16; }
 
+// One request's layer of at most 8 MB (by its table's capacity when the length
+// is on the device) in page planes of at most 8 KiB.
+bool small_layer(const Geometry& g, int32_t planes, int64_t tokens) {
+  int64_t bytes;
+  return g.plane_bytes <= 8192 && !__builtin_mul_overflow(g.row_bytes * planes, tokens, &bytes) && bytes <= (8 << 20);
+}
+
 // Shared launcher for the four movement entry points.
 //   pack:     direction (pool -> packed when true)
 //   seq_lens: device lengths (batched) or null (single request of n_single)
@@ -890,11 +897,16 @@ topkv_status_t launch_move(bool pack, const topkv_pool_t* pool, int32_t layer, v
 
   // One request's layer goes there too: a launch of one runs back to back with
   // the next without the 0.3-0.6 us that this file's grid leaves in between.
+  // Small layers of planes of up to 8 KiB stay here, in a small workgroup per
+  // plane (layers one after the other, us a launch, here against there: two heads
+  // of 256 bytes 4200 tokens (4.3 MB) 3.1 against 3.6, 6000 3.4 against 3.8, 8000 (8.2 MB) 4.4
+  // against 4.4, 10000 5.7 against 4.9; one head 10000 3.3 against 3.6).
   // So does a small window of a wide table: the chunk grid spans the window's
   // tokens only, where the page grid has a slot per table entry.
   const bool sparse = seq_lens && sparse_window(window, bt_stride, pool->page_size);
   if (plane_stride == 0 && layers == 1 &&
-      ((num_reqs == 1 && window == 0) || takes_chunks(g.plane_bytes, vb) ||
+      ((num_reqs == 1 && window == 0 && !small_layer(g, pool->planes, seq_lens ? tok_cap : n_single)) ||
+       takes_chunks(g.plane_bytes, vb) ||
        (sparse && window_takes_chunks(num_reqs, pool->planes, window, g.row_bytes)))) {
     bool launched = false;
     st = topkv_internal::chunk_move(pack, pool, layer, 1, packed, packed_cap, packed_cap, 0, num_reqs, tables, bt_stride,

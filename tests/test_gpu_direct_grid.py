@@ -244,6 +244,36 @@ def test_one_request_rows(tk, n):
     assert not to_host(packed).any() and np.array_equal(to_host(dst), dst_h), "a request that does not fit moved"
 
 
+
+# one request on both sides of the page grid's share (planes of 8 KiB, 8 MiB of layer) and of the rows grid's
+# change from 64 to 24 and 32 KiB tiles (16 MiB, 18 MiB and more)
+@pytest.mark.parametrize("H,D,n", [(2, 128, 40), (2, 128, 8192), (2, 128, 8193), (1, 128, 16384), (1, 129, 16384),
+                                   (8, 128, 4096), (8, 128, 4097), (8, 128, 4600), (8, 128, 4700)])
+def test_one_request_layer(tk, H, D, n):
+    P, P2, C = 16, 32, 2
+    say(f"[direct_grid] one request of {n} tokens, {H} heads of {D}")
+    rng = np.random.default_rng(n + H)
+    lens = np.array([n], dtype=np.int32)
+    (bt, NP), (bt2, NP2) = _tables(rng, lens, P), _tables(rng, lens, P2)
+    src_h, dst_h = _words(rng, NP * C * P * H * D, 2).reshape(1, NP, C, P, H, D), _words(rng, NP2 * C * P2 * H * D, 2).reshape(1, NP2, C, P2, H, D)
+    want, want_dst = oracle.pack_layer(src_h, 0, bt, lens), dst_h.copy()
+    oracle.unpack_layer(want, want_dst, 0, bt2, lens)
+    need = -(-n // P)
+    src, lensd, exact, exact2 = to_dev(src_h), to_dev(lens), to_dev(bt[:, :need].copy()), to_dev(bt2[:, :-(-n // P2)].copy())
+    for host_len in (False, True):
+        packed, dst = to_dev(np.zeros(want.size + 8, np.uint16)), to_dev(dst_h)
+        if host_len:
+            tk.topkv_pack_layer(src, 0, exact, n, packed)
+            tk.topkv_unpack_layer(packed, dst, 0, exact2, n)
+        else:
+            tk.topkv_pack_layer_batched(src, 0, 1, exact, exact.shape[1], lensd, packed, 2 * want.size)
+            tk.topkv_unpack_layer_batched(packed, dst, 0, 1, exact2, exact2.shape[1], lensd, 2 * want.size)
+        torch.cuda.synchronize()
+        got = to_host(packed)
+        assert np.array_equal(got[:want.size], want) and not got[want.size:].any(), "pack"
+        assert np.array_equal(to_host(dst), want_dst), "unpack"
+
+
 DIRECT_SLOTS = 8192                                          # most workgroups of a direct grid of device lengths
 # windows whose grid is longer than that although most requests are short
 WIDE_WINDOWS = [(1, 576, 2, 64, 16, [2, 0, 3100, 150, 64, 65] * 10, None, 1, 3000),
