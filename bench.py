@@ -180,19 +180,37 @@ def layer_bytes(wl, layer):
 
 
 def layer_kernel(wl, direction):
-    """The kernel a full-attention layer's launch runs: the library hands one
-    request with no window (a token's 16-byte pieces filling whole 64-lane
-    wave spans, the buffer holding the table's full bound) to the layout-move
-    kernel's direct grid, everything else to the fast kernels.  Fixed-state
-    layers run the state kernel."""
+    """The kernel that a full-attention layer's launch (or, where every layer has
+    a window, layer 0's) runs.  The rules of the library's plain launches, with
+    lengths on the device and buffers aligned as torch aligns them:
+      * one request's layer runs the rows kernel (rows of whole 16-byte chunks, a
+        page plane of whole 64-chunk spans), but for small layers of planes of at
+        most 8 KiB;
+      * page planes below 4 KiB, rows that are no multiple of 16 bytes and small
+        windows of wide tables run the layout-move kernel's direct grid, or the
+        live grid where that would be longer than 8192 workgroups;
+      * everything else runs the page kernels.
+    Fixed-state layers run the state kernel."""
     if wl.layer_state:
         return f"kv_{direction}_kernel (attention layers), kv_state_kernel (state layers)"
-    row = wl.num_heads * wl.head_dim * wl.elem_bytes
+    row, R = wl.num_heads * wl.head_dim * wl.elem_bytes, wl.num_reqs
     tables, page = (wl.block_tables, wl.page_size) if direction == "pack" else (wl.dst_block_tables, wl.dst_page_size)
-    full_bound = wl.num_reqs == 1 and tables.shape[1] * page <= int(wl.seq_lens[0])   # packed slice = the lengths
-    if full_bound and not any(wl.window(l) for l in range(wl.num_layers)) and row % (64 * 16) == 0:
-        return "kv_reshard_direct_kernel"
-    return f"kv_{direction}_kernel"
+    width, plane = tables.shape[1], page * row
+    W = min(wl.window(l) for l in range(wl.num_layers))
+    small = plane <= 8192 and wl.planes * width * page * row <= 8 << 20
+    sparse = W and (-(-W // page) + 1) * 4 <= width and R * wl.planes * W * row <= 32 << 20
+    chunks = plane < 4096 or row % 16 or sparse
+    if R > 1024 or not (chunks or (R == 1 and not W and not small)):
+        return f"kv_{direction}_kernel"
+    if R == 1 and not W and row % 16 == 0 and plane % 1024 == 0:
+        return "kv_rows_kernel"
+    per_unit = -(-plane // 16)                                   # 16-byte chunks of one page's plane
+    units = min(width, (W + page - 2) // page + 1) if W else width
+    vpt = 8 if per_unit % 64 == 0 else 2
+    grid = lambda v: -(-units * per_unit // (256 * v)) * wl.planes * R
+    while vpt > 1 and grid(vpt) < 512:
+        vpt //= 2
+    return "kv_reshard_live_kernel" if grid(vpt) > 8192 else "kv_reshard_direct_kernel"
 
 
 def table_layout(wl, layout):

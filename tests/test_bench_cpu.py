@@ -185,3 +185,32 @@ def test_kernel_launches_per_sweep():
     n_engine = sum(1 for kind, _, _ in st.chunks if kind == "engine")
     n_layer = sum(1 for kind, _, _ in st.chunks if kind == "layer")
     assert n_layer == 18 and bench.sweep_grids(st, "engine", 0) >= n_engine + n_layer
+
+
+def test_layer_kernel_follows_the_launch_rules():
+    """The kernel that the roofline object names for a layer's launch: one request, batches, small planes,
+    ragged rows and windows, with exact and wide tables."""
+    import bench
+    from paper_2607_28633_amd.workloads import make_workload
+
+    def kernel(name, direction="pack", width=None, windows=None, **over):
+        wl = make_workload(name, **over)
+        if windows is not None:
+            wl.layer_windows = (windows,) * wl.num_layers
+        if width:
+            wl.block_tables = np.full((wl.num_reqs, width // wl.page_size), -1, np.int32)
+            wl.dst_block_tables = np.full((wl.num_reqs, width // wl.dst_page_size), -1, np.int32)
+        return bench.layer_kernel(wl, direction)
+
+    assert kernel("llama3-70b-4k") == kernel("llama3-8b", "unpack") == "kv_rows_kernel"
+    assert kernel("llama3-70b-tp8") == "kv_pack_kernel"                       # 4 KiB planes, 2 MB
+    assert kernel("llama3-70b-tp8", seq_lens=[40000], num_layers=2) == "kv_rows_kernel"
+    for name in ("llama3-70b-batch8", "deepseek-v3-mla", "reblock-70b"):
+        assert kernel(name) == "kv_pack_kernel" and kernel(name, "unpack") == "kv_unpack_kernel"
+    assert kernel("gpt-oss-120b") == "kv_pack_kernel"                         # its full-attention layers
+    assert kernel("gpt-oss-120b", windows=128) == "kv_reshard_direct_kernel"  # 8 MB of window
+    assert kernel("gpt-oss-120b", windows=1000) == "kv_pack_kernel"           # 66 MB
+    assert kernel("tiny", page_size=8) == "kv_reshard_direct_kernel"          # 2 KiB planes
+    assert kernel("tiny", page_size=8, width=1 << 22) == "kv_reshard_live_kernel"
+    assert kernel("tiny", head_dim=25) == "kv_reshard_direct_kernel"          # 100-byte rows
+    assert kernel("qwen3.5-397b-hybrid").startswith("kv_pack_kernel (attention layers)")
