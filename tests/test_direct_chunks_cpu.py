@@ -1,5 +1,5 @@
-"""CPU model of the layout-move direct grid's index arithmetic (kv_reshard_direct_kernel
-of csrc/reshard.hip and the host's plan for it): units, 16-byte chunks, a run's last
+"""CPU model of the index arithmetic of the layout-move direct grid (kv_reshard_direct_kernel of
+csrc/reshard.hip and the host's plan for it), of the live grid's tiles and of the one-request rows grid: units, 16-byte chunks, a run's last
 chunk moved back to end with the run, runs that are short or cut by the packed capacity
 byte by byte, windows, packed capacities and shard regions.  Every access is
 checked against its buffer, and the bytes that arrive against the oracle's
@@ -179,7 +179,7 @@ def _case(seed, capped=False):
         shape = (2, NP, C, H, P, D) if kind == "hm" else (2, NP, C, P, H, D)
         data = npr.integers(0, 255, size=int(np.prod(shape)) * eb, dtype=np.uint8).view(dt).reshape(shape)
         sides.append((rs.POOL if kind == "pool" else rs.POOL_HEAD_MAJOR, data, rng.randint(0, 1), bt, rng.randint(0, H - hc)))
-    return dict(lens=lens, hc=hc, window=window, shards=shards, cap=cap, eb=eb, D=D, C=C, sides=sides, vpt=rng.choice([1, 2, 8]))
+    return dict(lens=lens, hc=hc, window=window, shards=shards, cap=cap, eb=eb, D=D, C=C, sides=sides, vpt=rng.choice([1, 2, 4, 8]))
 
 
 @pytest.mark.parametrize("chunk", range(8))
@@ -305,3 +305,53 @@ def test_live_grid_visits_every_tile_once(R):
             local = t - first[r]
             got.append((r, local // tiles, local % tiles))
         assert got == want
+
+
+@pytest.mark.parametrize("pack", [True, False])
+def test_rows_grid(pack):
+    """kv_rows_kernel: every early table lookup inside the row, every load inside its buffer, and the chunks that
+    arrive: one request's plane as one run of 16-byte chunks, pages outside the pool and chunks past the tokens left."""
+    rng = random.Random(11 + pack)
+    for trial in range(60):
+        per_token, planes = rng.choice([4, 16, 64, 72, 128]), rng.choice([1, 2])
+        P = 64 // math.gcd(64, per_token) * rng.choice([1, 2, 4])   # tokens a page: page planes of whole wave spans
+        per_page, vpt = P * per_token, rng.choice([1, 2, 3, 4, 6, 8, 12, 16])
+        n = rng.choice([0, 1, P, P + 1, rng.randint(1, 60)])
+        stride = max(1, -(-n // P)) + rng.choice([0, 0, 3])
+        pages = -(-n // P) + 2
+        table = [rng.choice([-1, pages + 5]) if rng.random() < 0.2 else x for x in rng.sample(range(pages), -(-n // P))]
+        table += [rng.choice([-7, 1 << 30]) for _ in range(stride - len(table))]
+        tok_cap, fits = stride * P, rng.random() < 0.9
+        total = min(max(n, 0), tok_cap) * per_token
+        max_total = total + rng.choice([0, 5]) if fits else total - 1
+        div = make_div(per_page)
+        pool_chunks, moved = pages * planes * per_page, {}
+        grid = -(-(tok_cap * per_token) // (vpt * NT))
+        for block in range(grid):
+            for c in range(planes):
+                for wave in range(4):
+                    base = block * NT * vpt + wave * 64
+                    look = fdiv(np.array([base + min(lane, vpt - 1) * NT for lane in range(64)]), div)
+                    look = np.minimum(look, stride - 1)
+                    assert (look >= 0).all() and (look < stride).all()
+                    if base >= total or total > max_total:
+                        continue
+                    for j in range(vpt):
+                        first, entry = base + j * NT, table[look[j]]
+                        usable = first < total and 0 <= entry < pages
+                        m = first - int(fdiv(first, div)) * per_page
+                        for lane in (0, 1, 63):
+                            at = c * per_page + (entry * planes * per_page + m if usable else 0) + lane
+                            load = at if pack else c * total + min(first + lane, total - 1)
+                            assert 0 <= load < (pool_chunks if pack else planes * total)
+                            if usable and first + lane < total:
+                                there, here = (at, c * total + first + lane)
+                                assert 0 <= there < pool_chunks and here < planes * total
+                                assert moved.setdefault(here, there) == there
+        want = {}
+        if total <= max_total:
+            for c in range(planes):
+                for q in range(total):
+                    if q % 64 in (0, 1, 63) and 0 <= table[q // per_page] < pages:
+                        want[c * total + q] = (table[q // per_page] * planes + c) * per_page + q % per_page
+        assert moved == want

@@ -2,6 +2,7 @@
 oracle: units of several page sizes, wave-uniform and per-lane spans, several granules, rows that are no
 multiple of 16 bytes or shorter than that, windows, each tile size, packed regions too small, and block
 tables much wider than their requests."""
+import math
 import sys
 
 import numpy as np
@@ -48,10 +49,10 @@ CASES = [
     (3, 3, 2, 16, 9, [1, 2, 143, 145], None, 1, 0),          # 18-byte rows
     (1, 6, 1, 16, 4, [1, 2, 3, 63, 64, 65], None, 1, 0),     # 6-byte rows: short last runs
     (1, 5, 1, 3, 3, [1, 2, 7, 30], None, 1, 0),              # units shorter than a chunk: the general grid
-    (8, 128, 2, 16, 64, [8192], None, 1, 0),                 # 32 KiB tiles, wave-uniform, one request
-    (1, 129, 2, 16, 16, [40000, 1, 39999], None, 1, 0),      # 32 KiB tiles, per lane
-    (8, 128, 2, 16, 16, [2047, 2048, 2049], None, 1, 0),     # 16 KiB tiles
-    (8, 128, 2, 16, 16, [640, 1], None, 1, 0),               # 8 KiB tiles
+    (8, 128, 2, 16, 64, [8192], None, 1, 0),                 # wave-uniform, one request: 8 chunks a lane
+    (1, 129, 2, 16, 16, [40000, 1, 39999], None, 1, 0),      # per lane, 2 chunks: the longest grids
+    (8, 128, 2, 16, 16, [2047, 2048, 2049], None, 1, 0),     # 8 chunks
+    (8, 128, 2, 16, 16, [640, 1], None, 1, 0),               # 1 chunk
     # head slices and shards
     (8, 128, 2, 16, 16, [100, 1, 33], (2, 2), 1, 0),
     (8, 128, 2, 16, 64, [100, 1, 33], (0, 8), 4, 0),
@@ -61,13 +62,55 @@ CASES = [
     (8, 64, 2, 16, 16, [1, 127, 128, 129, 500, 0], None, 1, 128),
     (1, 576, 2, 64, 16, [1, 100, 101, 164, 500], None, 1, 100),
     (7, 25, 2, 16, 24, [23, 24, 300, 700], None, 1, 17),
-    # windows of whole wave spans, one workgroup per CU: 3, 6, 12 and 16 chunks per lane
+    # windows of whole wave spans, 16 to 120 requests: 1, 1, 2 and 4 chunks per lane
     (1, 32, 2, 16, 16, [1023 + i for i in range(16)], None, 1, 1024),
     (1, 32, 2, 16, 16, [1000 + 3 * i for i in range(32)], None, 1, 1024),
     (1, 32, 2, 16, 16, [990 + 2 * i for i in range(64)], None, 1, 1024),
     (1, 32, 2, 16, 16, [i if i < 20 else 880 + i for i in range(120)], None, 1, 900),
     (1, 6, 1, 16, 4, [1, 9, 63, 64, 65], None, 1, 5),
+    # several granules: 2 and 4 chunks per lane of whole spans, 2 of lanes with a unit each
+    (8, 128, 2, 16, 64, [700, 650], (0, 8), 4, 0),
+    (8, 128, 2, 16, 64, [1500, 1400], (0, 8), 4, 0),
+    (6, 20, 2, 8, 16, [7000, 6990], (1, 4), 2, 0),
 ]
+
+
+def _plan(H, hc, head, P, P2, kind, lens, S, W, width=None):
+    """The host's plan for one move of a case: (whole wave spans, granules, chunks per lane or "live", workgroups)
+    of the direct or live grid, None for the general one.  kind: pack, unpack, unpack_hm, pool or pool_hm."""
+    hm = kind.endswith("hm")
+    per = 1 if hm else hc // S
+    gran, gpt = per * head, hc // per
+    heads, scattered = gpt > 1, gpt > 1 or kind.startswith("pool")
+    pages = [P] if kind == "pack" else [P2] if kind.startswith("unpack") else [P, P2]
+    unit = 1 if heads or hc != H else math.gcd(*pages)
+    if (gran if heads else unit * gran) < 16 or len(lens) > 1024:
+        return None
+    cpu = gpt * -(-gran // 16) if heads else -(-unit * gran // 16)
+    tok = min((width or (max(1, -(-max(lens) // p)) + 1)) * p for p in pages)
+    units = -(-tok // unit)
+    if W:
+        units = min(units, (W + unit - 2) // unit + 1)
+    grid = lambda v: -(-units * cpu // (v * 256)) * 2 * len(lens)
+    wave = cpu % 64 == 0
+    v = 2 if not wave else 4 if scattered else 8
+    while v > 1 and grid(v) < 512:
+        v //= 2
+    return (wave, heads, v if grid(v) <= 8192 else "live", grid(v))
+
+
+def test_cases_reach_every_tile_size():
+    """CASES together run every tile size of the direct grid that a batch can have, for each direction, whole
+    spans and lanes, one granule and several."""
+    seen = set()
+    for H, D, eb, P, P2, lens, sl, S, W in CASES:
+        for kind in ("pack", "unpack", "unpack_hm", "pool", "pool_hm"):
+            p = _plan(H, (sl or (0, H))[1], D * eb, P, P2, kind, lens, 1 if kind.startswith("pool") else S, W)
+            if p:
+                seen.add((kind.split("_")[0],) + p[:3])
+    want = {(way, wave, heads, v) for way in ("pack", "unpack", "pool") for wave in (False, True) for heads in (False, True)
+            for v in ((1, 2) if not wave else (1, 2, 4) if heads or way == "pool" else (1, 2, 4, 8))}
+    assert want <= seen, want - seen
 
 
 @pytest.mark.parametrize("case", range(len(CASES)))

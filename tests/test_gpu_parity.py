@@ -423,7 +423,9 @@ def _persistent_case(kind):
 def test_persistent_grid(tk, kind, window):
     """Batches beyond the direct grid's limits run the persistent grid (length
     scan, request search); pack and unpack, with and without a window, equal
-    the oracle."""
+    the oracle.  (Many slots with the window, whose capacity is small, run the
+    layout-move direct grid; larger windows in the persistent grid are
+    test_gpu_window.test_sparse_windows.)"""
     wl = _persistent_case(kind)
     say(f"[persistent] {kind}: {wl.num_reqs} requests, table width {wl.block_tables.shape[1]}, window {window}")
     src_h, dst_h = host_src_pool(wl), host_dst_prefill(wl)
@@ -571,4 +573,72 @@ def test_plane_tiles(tk, plane, R):
     torch.cuda.synchronize()
     got = to_host(packed)
     assert np.array_equal(got[:L * n], np.concatenate(want)) and not got[L * n:].any()
+    assert np.array_equal(to_host(dst), want_dst)
+
+
+def _many(rng, R, P):
+    """More requests than the direct grids take (up to 2 pages each), and a permuted pool."""
+    lens = np.array([[1, P - 1, 0, P, P + 1][r % 5] for r in range(R)], dtype=np.int32)
+    bt, at = np.full((R, 2), -1, dtype=np.int32), 0
+    need = [-(-int(n) // P) for n in lens]
+    perm = rng.permutation(sum(need) + 2).astype(np.int32)
+    for r, k in enumerate(need):
+        bt[r, :k] = perm[at:at + k]
+        at += k
+    return lens, bt, sum(need) + 2
+
+
+@pytest.mark.parametrize("offset,vec", [(0, 16), (8, 8), (4, 4), (2, 2), (1, 1)])
+def test_general_grid_whole_spans(tk, offset, vec):
+    """The layout-move kernel's general grid with tokens of whole wave spans: 1030 requests of 1 KiB rows, packed
+    at an offset that leaves vectors of `vec` bytes; pack and unpack of a layer and of half of its heads."""
+    P, C, H, D, R = 4, 2, 8, 128, 1030
+    rng = np.random.default_rng(offset)
+    lens, bt, NP = _many(rng, R, P)
+    say(f"[general_grid] {R} requests, packed at +{offset}")
+    import oracle.reshard as rs
+    src_h, dst_h = (rng.integers(0, 256, size=(1, NP, C, P, H, D), dtype=np.uint8) for _ in range(2))
+    src, btd, lensd = to_dev(src_h), to_dev(bt), to_dev(lens)
+    for first, heads in ((0, H), (2, 4)):
+        n = rs.packed_heads_elems(C, heads, D, lens)
+        want, want_dst = np.zeros(n, np.uint8), dst_h.copy()
+        rs.move_layer(rs.View(rs.POOL, src_h, 0, bt, first), rs.View(rs.PACKED, want), lens, heads)
+        rs.move_layer(rs.View(rs.PACKED, want), rs.View(rs.POOL, want_dst, 0, bt, first), lens, heads)
+        buf, dst = torch.zeros(offset + n + 16, dtype=torch.uint8, device="cuda"), to_dev(dst_h)
+        view = tk.packed_view(buf[offset:], nbytes=n)
+        tk.topkv_move_layer(tk.pool_view(src, 0, btd, 2, first), view, R, lensd, heads)
+        tk.topkv_move_layer(view, tk.pool_view(dst, 0, btd, 2, first), R, lensd, heads)
+        torch.cuda.synchronize()
+        got = to_host(buf)
+        assert np.array_equal(got[offset:offset + n], want) and not got[:offset].any() and not got[offset + n:].any()
+        assert np.array_equal(to_host(dst), want_dst)
+
+
+@pytest.mark.parametrize("row", [24, 20, 6, 5])
+def test_narrow_vectors_persistent(tk, row):
+    """Page kernels of 8, 4, 2 and 1 byte vectors in the persistent grids: 1030 requests of rows that are no
+    multiple of 16 bytes, plain layers and the layer engine."""
+    P, C, L, R = 16, 2, 2, 1030
+    rng = np.random.default_rng(row)
+    lens, bt, NP = _many(rng, R, P)
+    say(f"[narrow] {R} requests of {row}-byte rows")
+    src_h = rng.integers(0, 256, size=(L, NP, C, P, 1, row), dtype=np.uint8)
+    want, want_dst = [oracle.pack_layer(src_h, l, bt, lens) for l in range(L)], np.zeros_like(src_h)
+    for l in range(L):
+        oracle.unpack_layer(want[l], want_dst, l, bt, lens)
+    n, src, btd, lensd = want[0].size, to_dev(src_h), to_dev(bt), to_dev(lens)
+    packed, dst = torch.zeros((L, n + 32 - n % 16), dtype=torch.uint8, device="cuda"), to_dev(np.zeros_like(src_h))
+    for l in range(L):
+        tk.topkv_pack_layer_batched(src, l, R, btd, 2, lensd, packed[l, :n])
+        tk.topkv_unpack_layer_batched(packed[l, :n], dst, l, R, btd, 2, lensd)
+    torch.cuda.synchronize()
+    got = to_host(packed)
+    assert all(np.array_equal(got[l, :n], want[l]) and not got[l, n:].any() for l in range(L))
+    assert np.array_equal(to_host(dst), want_dst)
+    packed, dst, step = torch.zeros_like(packed), torch.zeros_like(dst), packed.shape[1]
+    tk.topkv_engine_pack_layers(src, 0, L, R, btd, 2, lensd, packed, step)
+    tk.topkv_engine_unpack_layers(packed, step, dst, 0, L, R, btd, 2, lensd)
+    torch.cuda.synchronize()
+    got = to_host(packed)
+    assert all(np.array_equal(got[l, :n], want[l]) and not got[l, n:].any() for l in range(L))
     assert np.array_equal(to_host(dst), want_dst)
