@@ -52,9 +52,6 @@ namespace topkv_reshard {
 #ifndef TOPKV_RS_SLOTS
 #define TOPKV_RS_SLOTS 8192       // direct grids of device lengths: most workgroups; more run the live grid
 #endif
-#ifndef TOPKV_RS_LIVE_PER_CU
-#define TOPKV_RS_LIVE_PER_CU 24   // live grid: workgroups per CU
-#endif
 #ifndef TOPKV_RS_WG_PER_CU
 #define TOPKV_RS_WG_PER_CU 16     // grid cap = CUs * this
 #endif
@@ -668,27 +665,27 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(
 }
 
 // The live grid: the same tiles in a grid that follows the lengths instead of
-// the table's width.  A few workgroups per CU stride over the tiles that have
-// tokens; each scans the lengths once into the requests' live tiles and kept
-// tokens (exclusive prefix sums in LDS) and finds a tile's request with two
-// ballots.  It takes the moves whose direct grid would have more than
-// TOPKV_RS_SLOTS workgroups.
+// the table's width.  Workgroups stride over the tiles that have tokens; each
+// scans the lengths once into the requests' live tiles and kept tokens
+// (exclusive prefix sums in LDS) and finds a tile's request with two ballots.
+// It takes the moves whose direct grid would have more than TOPKV_RS_SLOTS
+// workgroups.
 // A slot past its request's tokens costs the direct grid 0.41 ns, so tables
 // wider than their requests, and batches of uneven ones, would cost more than
 // the data.  us a launch, direct grid -> live grid: slices of two of eight
 // heads, 64 requests of 1000 tokens in tables of 32768 113 -> 25, of 131072
-// 419 -> 25; 128 requests around 512 tokens (sigma 1) in a table that fits the
-// longest 56 -> 35; MLA re-block, 64 x 1000 in 32768 100 -> 29; head-major, the
-// same, 262 -> 91.  Tables that the requests fill are 2 to 10% faster in the
-// direct grid (slices 64 x 1000, 8064 workgroups, 22.8 against 25.2, 256 x 1000
-// 89 against 93; head-major 64 x 1000 88.7 against 90.7, 256 x 1000 (1 GB) 356
-// against 372; 8 layers into one-token pages, 64 x 1000, 183 against 202), but
-// the host doesn't know how full they are.  At the line a launch of dead slots
-// costs the direct grid 3.4 us.
+// 419 -> 25, 64 x 100 in 32768 106 -> 5.8; 128 requests around 512 tokens (sigma
+// 1) in a table that fits the longest 56 -> 35; MLA re-block, 64 x 1000 in 32768
+// 99 -> 30; head-major, the same, 262 -> 90.  Where the requests fill their
+// tables the two are even (slices 256 x 1000 89.7 and 89.4, head-major 355 and
+// 356, 8 layers into one-token pages 184 and 188) but for the scan of a shorter
+// launch (slices 64 x 1000, 8064 workgroups, 22.7 and 25.2): at the line a launch
+// of dead slots costs the direct grid 3.4 us.
+// One tile a workgroup, as far as the host can tell how many there are
+// (live_workgroups): a workgroup that goes on to another tile is slower
+// (2056-byte rows, 256 x 1000, 1 GB: 385 us in 24 workgroups per CU, 371 in 64,
+// 362 in 128, one tile each), one too many costs 0.65 ns.
 // 4 chunks per lane: slices 64 x 1000 25.0 us with 2, 24.3 with 4, 24.8 with 8.
-// 24 workgroups per CU: head-major 256 x 1000 391 us with 8, 374 with 16, 372
-// with 24, 369 with 32; each costs a short move its scan (slices, 64 x 100 in a
-// wide table, 5.0 us with 4, 8.2 with 24, 9.7 with 32).
 __device__ void live_prefix(const Params& p, const int32_t* __restrict__ seq_lens, uint32_t tile, int32_t* first,
                             int32_t* kept, int32_t* lens, uint64_t* wsum) {
   const int lane = threadIdx.x & 63;
@@ -1000,6 +997,17 @@ RowsFn rows_kernel_for(bool pack, bool host_len, int vpt) {
   return pack ? rows_kernel_vpt<true, false>(vpt) : rows_kernel_vpt<false, false>(vpt);
 }
 
+// Workgroups of a live grid that has at most `tiles` live tiles in `layers`
+// layers: one for each.  With a packed side, whose size follows the batch, up to
+// 128 per CU, or 32 and a layer; between pools, whose size doesn't (a big pool
+// and a few short requests would be all dead workgroups), up to 32 per CU and
+// layer, else 24 per CU that go on to further tiles.  At 32 per CU the dead ones
+// take 5 us at most, which the general grid takes for its smallest launch.
+int64_t live_workgroups(int64_t tiles, int64_t layers, int64_t cus, bool pools) {
+  const int64_t most = pools || layers > 4 ? 32 * cus * layers : 128 * cus;
+  return tiles <= most ? tiles : pools ? 24 * cus : most;
+}
+
 int64_t gcd(int64_t a, int64_t b) {
   while (b) {
     const int64_t r = a % b;
@@ -1255,8 +1263,16 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
       int cus = 0;
       const topkv_status_t st = cu_count(&cus);
       if (st != TOPKV_OK) return st;
-      const int64_t most = (int64_t)cus * TOPKV_RS_LIVE_PER_CU;
-      grid = dim3((unsigned)(workgroups(kLiveVpt) < most ? workgroups(kLiveVpt) : most));
+      // Tokens that can move: those of the tables, of the packed bytes, and of
+      // the destination pool, whose pages are named once.
+      int64_t tokens = (int64_t)num_reqs * max_tok;
+      if (dir != kPools && packed_cap / (geo->planes * (gpt / shards) * gran) < tokens)
+        tokens = packed_cap / (geo->planes * (gpt / shards) * gran);
+      if (dir != kPack && dst->pool.num_pages * (int64_t)dst->pool.page_size < tokens)
+        tokens = dst->pool.num_pages * (int64_t)dst->pool.page_size;
+      const int64_t tiles = ((tokens / unit + num_reqs) * cpu / (kLiveVpt * kThreads) + num_reqs) * geo->planes * layers;
+      grid = dim3((unsigned)live_workgroups(tiles < workgroups(kLiveVpt) ? tiles : workgroups(kLiveVpt), layers, cus,
+                                            dir == kPools));
       lds = sizeof(uint64_t) * kWaves + sizeof(int32_t) * (3 * (size_t)num_reqs + 1);
       uint32_t count = (uint32_t)layers;
       void* args[] = {&p.src.tables, &p.dst.tables, &seq_lens, &count, &p};
