@@ -552,11 +552,11 @@ topkv_status_t topkv_move_layer(const topkv_view_t* src, const topkv_view_t* dst
  * shard regions of `bytes` each), so with num_layers > 1 the stride is at
  * least max(1, shards) * bytes and the buffer spans (num_layers - 1) *
  * packed_layer_stride plus one layer's regions.  The layers go out as
- * hardware-dispatched grids of topkv_engine_layers_per_grid layers (the
- * bytes of one layer's packed regions, or for pool to pool the source
- * tables' capacity) where a direct grid applies (no window, whole wave
- * spans per token), else one launch per layer.  num_layers == 0 or
- * num_reqs == 0 queues nothing.  Extra errors: TOPKV_ERR_INVALID_ARG for a
+ * grids of topkv_engine_layers_per_grid layers (the bytes of one layer's
+ * packed regions, or for pool to pool the source tables' capacity) for up
+ * to 1024 requests (num_reqs * layers of a grid up to 65535) whose tokens
+ * are moved in runs of at least 16 bytes, with or without a window; else
+ * one launch per layer.  num_layers == 0 or num_reqs == 0 queues nothing.  Extra errors: TOPKV_ERR_INVALID_ARG for a
  * negative num_layers or stride, a layer range outside a pool, or a stride
  * that would overlap consecutive layers' packed regions. */
 topkv_status_t topkv_move_layers(const topkv_view_t* src, const topkv_view_t* dst, int32_t num_layers,

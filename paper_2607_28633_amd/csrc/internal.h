@@ -7,9 +7,10 @@
 namespace topkv_internal {
 
 // A plain pack (pool -> packed, every head) or unpack (packed -> pool) of
-// layers [layer, layer + layers), run by the layout-move kernel's direct grid
-// when that grid applies: layer z's packed block starts at packed + z *
-// layer_stride and holds min(layer_cap, total_cap - z * layer_stride) bytes,
+// layers [layer, layer + layers), run by the layout-move kernels' grids for
+// up to 1024 requests (rows, direct or live) when one applies: layer z's
+// packed block starts at packed + z * layer_stride and holds
+// min(layer_cap, total_cap - z * layer_stride) bytes,
 // and a request that does not fit it is not moved.  The lengths are the
 // device values seq_lens, or (one request) seq_len when seq_lens is null.
 // *launched tells whether it launched; when it did not, nothing was queued

@@ -1017,12 +1017,12 @@ int64_t gcd(int64_t a, int64_t b) {
   return a;
 }
 
-// direct_only: launch only the direct grid (and report whether it did through
-// *launched), for a plain pack or unpack whose caller has its own kernels;
-// otherwise whichever grid applies.  layers > 1: the views' layers and the
-// next layers - 1 on grid z of a direct grid (a pool side's layer slabs follow
-// each other; a packed side's layer z starts at data + z *
-// packed_layer_stride), launched only when a direct grid applies: *launched
+// direct_only: launch only a grid of up to 1024 requests (rows, direct or live;
+// *launched reports whether it did), for a plain pack or unpack whose caller
+// has its own kernels; otherwise whichever grid applies.  layers > 1: the
+// views' layers and the next layers - 1 in one direct or live grid (a pool
+// side's layer slabs follow each other; a packed side's layer z starts at data
+// + z * packed_layer_stride), launched only when one of them applies: *launched
 // stays false otherwise, with nothing queued.  The caller has checked the
 // layer ranges and the stride.  total_cap >= 0: packed bytes of all layers
 // together; strict: requests that do not fit their layer's packed bytes are
@@ -1035,7 +1035,7 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
   *launched = false;
   if (!src || !dst || !valid_layout(src->layout) || !valid_layout(dst->layout)) return TOPKV_ERR_INVALID_ARG;
   if (src->layout == TOPKV_LAYOUT_PACKED && dst->layout == TOPKV_LAYOUT_PACKED) return TOPKV_ERR_INVALID_ARG;
-  // a host-side length (n_host >= 0) stands for seq_lens: one request, one-request grid only
+  // a host-side length (n_host >= 0) stands for seq_lens: one request of a plain pack or unpack
   const bool host_len = n_host >= 0;
   if (host_len && (num_reqs != 1 || !direct_only || seq_lens)) return TOPKV_ERR_INVALID_ARG;
   if (num_reqs < 0 || head_count <= 0 || window < 0 || (num_reqs > 0 && !seq_lens && !host_len))
@@ -1331,7 +1331,7 @@ topkv_status_t move_layer(const topkv_view_t* src, const topkv_view_t* dst, int3
 // side's layer z at data + z * packed_layer_stride), in grids of
 // topkv_engine_layers_per_grid layers (the bytes a layer moves: the packed
 // side's regions, or for pool to pool the source tables' capacity); a move
-// no direct grid takes runs one launch per layer.
+// that neither a direct nor a live grid takes runs one launch per layer.
 topkv_status_t move_layers(const topkv_view_t* src, const topkv_view_t* dst, int32_t num_layers,
                            int64_t packed_layer_stride, int32_t num_reqs, const int32_t* seq_lens,
                            int32_t head_count, int32_t window, hipStream_t stream) {
@@ -1385,7 +1385,7 @@ topkv_status_t move_layers(const topkv_view_t* src, const topkv_view_t* dst, int
                               : TOPKV_OK;
     if (st != TOPKV_OK) return st;
     if (launched) continue;
-    // one launch per layer (one layer in this group, or a move no direct grid takes)
+    // one launch per layer (one layer in this group, or a move that only the general grid takes)
     for (int32_t l = 0; l < n; ++l) {
       topkv_view_t s1 = s, d1 = d;
       topkv_view_t* one[2] = {&s1, &d1};

@@ -831,7 +831,13 @@ bool window_takes_chunks(int64_t num_reqs, int32_t planes, int32_t window, int64
 // against 6.5).
 // Rows or bases that are no multiple of 16 bytes (vb < 16) go there as well:
 // its 16-byte chunks need no alignment, where this file's vectors shrink to 8,
-// 4, 2 or 1 bytes (8 requests of 350-byte rows, 26 MB a launch: 13.3 -> 7.9 us).
+// 4, 2 or 1 bytes (8 requests of 350-byte rows, 26 MB a launch: 13.3 -> 7.9 us;
+// of 1032-byte rows, 8-byte aligned, 4096 tokens 31.8 -> 25.7).  Vectors of 8
+// bytes lose the least to that, so long rows of full tables are about even
+// (64 requests of 1000 tokens, 2056 bytes each: 90 -> 91 us; 4104 bytes up to a
+// tenth slower), but uneven batches and wide tables gain everywhere (2056 bytes:
+// 128 uneven requests 208 -> 132, 64 of 100 tokens in a wide table 198 -> 12.6;
+// 4104 bytes uneven 377 -> 300).
 bool takes_chunks(int64_t plane_bytes, int vb) { return plane_bytes < TOPKV_CHUNK_PLANE || vb < 16; }
 
 // One request's layer of at most 8 MB (by its table's capacity when the length

@@ -317,10 +317,9 @@ def test_move_layers_matches_oracle(tk, case, window):
     """topkv_move_layers over every layer of a range equals the oracle's move
     of each layer: head-sliced pack into packed layers `stride` apart (slack
     between them untouched), two shards per layer, the unpack back into a
-    pool, and pool-to-pool re-blocking from a later source layer.  With 2 KiB
-    rows the direct grid carries the layers on grid z (one request: the
-    one-request grid; a batch: the batched one); with 256-byte rows, or a
-    window, every layer takes its own launch."""
+    pool, and pool-to-pool re-blocking from a later source layer, for one
+    request and for a batch: one direct grid carries the layers on grid z,
+    whatever the rows, with a window or without."""
     wl = WORKLOADS[case]()
     C, H, D = _geom(wl)
     L = wl.num_layers + 1
