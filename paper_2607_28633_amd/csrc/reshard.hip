@@ -60,7 +60,7 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kVpt = TOPKV_RS_VPT;
 constexpr int kWgPerCu = TOPKV_RS_WG_PER_CU;
-constexpr int kLiveVpt = 4;       // live grid: chunks per lane
+constexpr int kLiveVpt = 4;       // live grid: chunks per lane (large moves between pools: twice that)
 
 template <int B> struct Vec;
 template <> struct Vec<16> { typedef unsigned int type __attribute__((ext_vector_type(4))); };
@@ -685,7 +685,10 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_direct_kernel(
 // (live_workgroups): a workgroup that goes on to another tile is slower
 // (2056-byte rows, 256 x 1000, 1 GB: 385 us in 24 workgroups per CU, 371 in 64,
 // 362 in 128, one tile each), one too many costs 0.65 ns.
-// 4 chunks per lane: slices 64 x 1000 25.0 us with 2, 24.3 with 4, 24.8 with 8.
+// 4 chunks per lane: slices 64 x 1000 25.0 us with 2, 24.3 with 4, 24.8 with 8;
+// two TP2 shards, 64 x 4096, one tile a workgroup 372 with 4, 376 with 8.  8 only
+// for wave spans between pools that must go on to further tiles: half as many
+// (re-block 16 -> 64, 64 x 4096, 1 GB: 432 -> 424; four layers of 16 x 4096 215 -> 208).
 __device__ void live_prefix(const Params& p, const int32_t* __restrict__ seq_lens, uint32_t tile, int32_t* first,
                             int32_t* kept, int32_t* lens, uint64_t* wsum) {
   const int lane = threadIdx.x & 63;
@@ -744,12 +747,12 @@ __device__ __forceinline__ int32_t tile_owner(const int32_t* first, int32_t num_
   return group + __popcll(__ballot(in && first[in ? b : 0] <= t)) - 1;
 }
 
-template <int kDir, bool kWave, bool kHeads>
+template <int kDir, bool kWave, bool kHeads, int VPT>
 __global__ __launch_bounds__(kThreads) void kv_reshard_live_kernel(const int32_t* __restrict__ src_tables,
                                                                    const int32_t* __restrict__ dst_tables,
                                                                    const int32_t* __restrict__ seq_lens, uint32_t layers,
                                                                    Params p) {
-  constexpr uint32_t kTile = (uint32_t)kThreads * kLiveVpt;
+  constexpr uint32_t kTile = (uint32_t)kThreads * VPT;
   extern __shared__ uint64_t lds_u64[];
   int32_t* const first = reinterpret_cast<int32_t*>(lds_u64 + kWaves);   // [num_reqs + 1]
   int32_t* const kept = first + p.num_reqs + 1;                          // [num_reqs]
@@ -766,9 +769,9 @@ __global__ __launch_bounds__(kThreads) void kv_reshard_live_kernel(const int32_t
     const uint32_t local = t - (uint32_t)__builtin_amdgcn_readfirstlane(first[r]);
     const uint32_t tiles = (uint32_t)__builtin_amdgcn_readfirstlane(first[r + 1] - first[r]) / (uint32_t)p.planes;
     const uint32_t c = local / tiles;
-    move_tile<kDir, kWave, kHeads, false, true, kLiveVpt>(src_tables, dst_tables, seq_lens, 0, 0, 0, 0,
-                                                          (uint32_t)p.src.bt_stride, (uint32_t)p.dst.bt_stride, 0, 0, p,
-                                                          LiveTile{lz, c, (local - c * tiles) * kTile, n, before, r});
+    move_tile<kDir, kWave, kHeads, false, true, VPT>(src_tables, dst_tables, seq_lens, 0, 0, 0, 0,
+                                                     (uint32_t)p.src.bt_stride, (uint32_t)p.dst.bt_stride, 0, 0, p,
+                                                     LiveTile{lz, c, (local - c * tiles) * kTile, n, before, r});
   }
 }
 
@@ -963,11 +966,16 @@ typedef void (*LiveFn)(const int32_t*, const int32_t*, const int32_t*, uint32_t,
 
 template <int kDir>
 LiveFn live_kernel_dir(bool wave, bool heads) {
-  if (heads) return wave ? kv_reshard_live_kernel<kDir, true, true> : kv_reshard_live_kernel<kDir, false, true>;
-  return wave ? kv_reshard_live_kernel<kDir, true, false> : kv_reshard_live_kernel<kDir, false, false>;
+  if (heads)
+    return wave ? kv_reshard_live_kernel<kDir, true, true, kLiveVpt> : kv_reshard_live_kernel<kDir, false, true, kLiveVpt>;
+  return wave ? kv_reshard_live_kernel<kDir, true, false, kLiveVpt> : kv_reshard_live_kernel<kDir, false, false, kLiveVpt>;
 }
 
-LiveFn live_kernel_for(int dir, bool wave, bool heads) {
+// vpt: kLiveVpt, or twice that (wave spans between pools)
+LiveFn live_kernel_for(int dir, bool wave, bool heads, int vpt) {
+  if (vpt > kLiveVpt)
+    return heads ? kv_reshard_live_kernel<kPools, true, true, 2 * kLiveVpt>
+                 : kv_reshard_live_kernel<kPools, true, false, 2 * kLiveVpt>;
   switch (dir) {
     case kPack: return live_kernel_dir<kPack>(wave, heads);
     case kUnpack: return live_kernel_dir<kUnpack>(wave, heads);
@@ -997,15 +1005,17 @@ RowsFn rows_kernel_for(bool pack, bool host_len, int vpt) {
   return pack ? rows_kernel_vpt<true, false>(vpt) : rows_kernel_vpt<false, false>(vpt);
 }
 
-// Workgroups of a live grid that has at most `tiles` live tiles in `layers`
-// layers: one for each.  With a packed side, whose size follows the batch, up to
-// 128 per CU, or 32 and a layer; between pools, whose size doesn't (a big pool
-// and a few short requests would be all dead workgroups), up to 32 per CU and
-// layer, else 24 per CU that go on to further tiles.  At 32 per CU the dead ones
-// take 5 us at most, which the general grid takes for its smallest launch.
-int64_t live_workgroups(int64_t tiles, int64_t layers, int64_t cus, bool pools) {
-  const int64_t most = pools || layers > 4 ? 32 * cus * layers : 128 * cus;
-  return tiles <= most ? tiles : pools ? 24 * cus : most;
+// The most workgroups of a live grid that are still one for each tile.  With a
+// packed side, whose size follows the batch, 256 per CU (lanes that find their
+// own units, which gain less: 128), or 32 and a layer.  Between pools, whose size
+// doesn't (a big pool and a few short requests would be all dead workgroups), 32
+// per CU and layer: the dead ones take 5 us at most, which the general grid takes
+// for its smallest launch.  us a launch at 128, 256 and 512 per CU: two TP2
+// shards, 64 x 4096 (1 GB) 390, 372, 372; head-major 100 uneven requests (2.6 GB)
+// 917, 878, 854.
+int64_t live_most(int64_t layers, int64_t cus, bool pools, bool wave) {
+  const int64_t most = pools ? 32 * layers : wave ? 256 : 128;
+  return cus * (most > 32 * layers ? most : 32 * layers);
 }
 
 int64_t gcd(int64_t a, int64_t b) {
@@ -1270,13 +1280,18 @@ topkv_status_t move_layer_impl(const topkv_view_t* src, const topkv_view_t* dst,
         tokens = packed_cap / (geo->planes * (gpt / shards) * gran);
       if (dir != kPack && dst->pool.num_pages * (int64_t)dst->pool.page_size < tokens)
         tokens = dst->pool.num_pages * (int64_t)dst->pool.page_size;
-      const int64_t tiles = ((tokens / unit + num_reqs) * cpu / (kLiveVpt * kThreads) + num_reqs) * geo->planes * layers;
-      grid = dim3((unsigned)live_workgroups(tiles < workgroups(kLiveVpt) ? tiles : workgroups(kLiveVpt), layers, cus,
-                                            dir == kPools));
+      auto tiles = [&](int v) {
+        const int64_t t = ((tokens / unit + num_reqs) * cpu / (v * kThreads) + num_reqs) * geo->planes * layers;
+        return t < workgroups(v) ? t : workgroups(v);
+      };
+      const int64_t most = live_most(layers, cus, dir == kPools, wave);
+      vpt = dir == kPools && wave && tiles(kLiveVpt) > most ? 2 * kLiveVpt : kLiveVpt;
+      // tiles past `most`: the workgroups go on to further ones, between pools in one round of them
+      grid = dim3((unsigned)(tiles(vpt) <= most ? tiles(vpt) : dir == kPools ? 24 * (int64_t)cus : most));
       lds = sizeof(uint64_t) * kWaves + sizeof(int32_t) * (3 * (size_t)num_reqs + 1);
       uint32_t count = (uint32_t)layers;
       void* args[] = {&p.src.tables, &p.dst.tables, &seq_lens, &count, &p};
-      const void* f = reinterpret_cast<const void*>(live_kernel_for(dir, wave, heads));
+      const void* f = reinterpret_cast<const void*>(live_kernel_for(dir, wave, heads, vpt));
       const hipError_t e = launch.start || launch.stop
                                ? hipExtLaunchKernel(f, grid, threads, args, lds, launch.stream, launch.start, launch.stop, 0)
                                : hipLaunchKernel(f, grid, threads, args, lds, launch.stream);

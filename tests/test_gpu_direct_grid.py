@@ -360,6 +360,46 @@ def test_small_planes_in_wide_tables(tk, short, monkeypatch):
     test_small_planes(tk, 2, 128, 2, 1, 16, short)
 
 
+@pytest.mark.parametrize("head_major", [False, True])
+@pytest.mark.parametrize("full", [False, True])
+def test_large_moves_between_pools(tk, full, head_major):
+    """Moves between pools past 32 tiles of 4 chunks per compute unit take tiles of 8: as many workgroups as
+    the destination pool holds tiles (short requests, most of them with nothing to do), or 24 per compute
+    unit that go on to further tiles (requests that fill the pool)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    H, D, C, P, P2, R = 8, 128, 2, 16, 64, 45
+    tile = 4 * 256 * 16 // (H * D * 2)                          # tokens of one plane in 4 chunks a lane
+    most = 32 * cus * tile // C                                 # tokens of as many tiles
+    rng = np.random.default_rng(17 + full)
+    lens = [(most * 2 // R & ~63) + int(k) for k in rng.integers(1, 64, size=R)] if full else \
+        [int(k) for k in rng.choice([0, 1, 15, 16, 17, 63, 64, 65, 130], size=R)]
+    width = max(lens) if full else 2 * most // R
+    pools = []
+    for page in (P, P2):
+        need = [-(-n // page) for n in lens]
+        NP = max(sum(need) + 3, most * 5 // 4 // page)
+        bt = np.full((R, -(-width // page) + 1), NP, dtype=np.int32)      # entries past a request: outside the pool
+        perm, at = rng.permutation(NP).astype(np.int32), 0
+        for r, k in enumerate(need):
+            bt[r, :k] = perm[at:at + k]
+            at += k
+        pools.append((bt, NP, to_dev(bt)))
+    (bt, NP, bt_d), (bt2, NP2, bt2_d) = pools
+    src = torch.randint(-32768, 32768, (1, NP, C, P, H, D), dtype=torch.int16, device="cuda")
+    dst = torch.full((1, NP2, C, H, P2, D) if head_major else (1, NP2, C, P2, H, D), 0x5A5A, dtype=torch.int16, device="cuda")
+    want = dst.clone()
+    rows = want[0].transpose(2, 3) if head_major else want[0]            # [page, plane, slot, head, dim]
+    for r, n in enumerate(lens):
+        t = torch.arange(n, device="cuda")
+        rows[bt2_d[r].long()[t // P2], :, t % P2] = src[0, bt_d[r].long()[t // P], :, t % P]
+    say(f"[direct] between pools: {sum(lens)} tokens of {R} requests, pool of {NP2 * P2}, head-major {head_major}")
+    tk.prepare_move_layer(tk.pool_view(src, 0, bt_d, bt.shape[1]),
+                          tk.pool_view(dst, 0, bt2_d, bt2.shape[1], head_major=head_major),
+                          R, to_dev(np.array(lens, dtype=np.int32)), H)()
+    torch.cuda.synchronize()
+    assert torch.equal(dst, want)
+
+
 def _us(call, n=30):
     for _ in range(3):
         call()
